@@ -37,6 +37,8 @@ struct GridDev {
   int32_t coarse;
   float* dxc;
   int64_t nsamp;
+  int64_t last_pair;  // last row at which two consecutive table rows can be read: rows - 2
+  int32_t next_row;   // 1: the second row of an active x-pair is the next table row (not hashed)
 };
 
 // Float offset of element i of a vector stored in runs of 16 values separated
@@ -60,6 +62,9 @@ inline void make_grid_dev(const fhash_index* idx, GridDev* g) {
   g->coarse = 0;
   g->dxc = nullptr;
   g->nsamp = 0;
+  const int64_t rows = idx->slot_offset[gd.n_levels];
+  g->last_pair = rows > 2 ? rows - 2 : 0;
+  g->next_row = idx->hash_bits == 0 ? 1 : 0;
   for (int l = 0; l < FHASH_MAX_LEVELS; ++l) {
     LevelDev& d = g->lv[l];
     if (l < gd.n_levels) {
@@ -238,6 +243,105 @@ __device__ __forceinline__ void corner_pair(const LevelDev& d, const ulonglong2*
       dir[d.dir_off + (int64_t)((btz * d.wv + (bit0 >> 6)) * d.by + (y >> 1))];
   s0 = entry_slot(e, bit0 & 63, d.slot_off, v0);
   s1 = entry_slot(e, (bit0 & 63) + (1 << a), d.slot_off, v1);
+}
+
+// The cell of a sample on one level and its in-cell fractions.
+struct Cell {
+  int x, y, z, t;
+  float fx, fy, fz, ft;
+};
+
+__device__ __forceinline__ Cell locate_cell(const LevelDev& d, const float4 p) {
+  Cell c;
+  locate(p.x, d.rx, d.sx, c.x, c.fx);
+  locate(p.y, d.ry, d.sy, c.y, c.fy);
+  locate(p.z, d.rz, d.sz, c.z, c.fz);
+  locate(p.w, d.rt, d.st, c.t, c.ft);
+  return c;
+}
+
+// Weight of vertex row r = (dy, dz, dt) of a cell (the x weights left out).
+__device__ __forceinline__ float row_weight(const Cell& c, int r) {
+  const int dy = r & 1, dz = (r >> 1) & 1, dt = (r >> 2) & 1;
+  return (dy ? c.fy : 1.0f - c.fy) * (dz ? c.fz : 1.0f - c.fz) * (dt ? c.ft : 1.0f - c.ft);
+}
+
+// Rows layout: the 8 x-pairs of a cell, looked up together.  The lookups of a
+// cell are independent, but written one row after another with the word
+// boundary as a branch inside each (row_pair_slots) they cannot overlap: every
+// row then waits for its own directory entry, and a level costs 8 to 16
+// memory latencies in a chain.  RowEntries holds the 8 entries (nxt: bit r,
+// vertex x + 1 of row r when it opens the next word), so a level costs one.
+struct RowEntries {
+  ulonglong2 e[8];
+  uint32_t nxt;
+};
+
+__device__ __forceinline__ void row_fetch(const LevelDev& d, const ulonglong2* dir, bool active,
+                                          const Cell& c, RowEntries& q) {
+  q.nxt = 0;
+  if (d.hash_bits || !active) return;
+  const ulonglong2* w =
+      dir + (d.dir_off + (int64_t)(((c.t * d.rz + c.z) * d.wv + (c.x >> 6)) * d.ry + c.y));
+  const int64_t dz = d.wv * d.ry, dt = (int64_t)d.rz * dz;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) q.e[r] = w[(r & 1) + ((r >> 1) & 1) * dz + (r >> 2) * dt];
+  if ((c.x & 63) == 63) {
+    w += d.ry;
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      q.nxt |= (uint32_t)(w[(r & 1) + ((r >> 1) & 1) * dz + (r >> 2) * dt].x & 1ull) << r;
+  }
+}
+
+// The slots of the 8 pairs: s[r] of vertex x of row r (v bit r: active), and
+// of vertex x + 1 (v bit 8 + r) pair_second.  The ranks of a vertex row are
+// consecutive, across its words too, so x + 1 follows x when x is active and
+// takes its place when it is not; a hashed row differs from x's by hx.
+struct RowPairs {
+  int64_t s[8];
+  uint32_t v, hx;
+};
+
+__device__ __forceinline__ void row_slots(const LevelDev& d, bool active, const Cell& c,
+                                          const RowEntries& q, RowPairs& p) {
+  if (d.hash_bits) {
+    const uint32_t mask = (1u << d.hash_bits) - 1u;  // hash_bits <= 31
+    p.v = 0xffffu;
+    p.hx = ((uint32_t)c.x ^ ((uint32_t)c.x + 1u)) & mask;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const uint32_t y = c.y + (r & 1), z = c.z + ((r >> 1) & 1), t = c.t + (r >> 2);
+      p.s[r] = d.slot_off + spatial_hash((uint32_t)c.x, y * 2654435761u ^ z * 805459861u ^
+                                                            t * 3674653429u, mask);
+    }
+    return;
+  }
+  p.hx = 0;
+  if (!active) {
+    p.v = 0xffffu;
+    const int64_t dz = (int64_t)d.ry * d.rx, dt = dz * d.rz;
+    const int64_t s = d.slot_off + ((int64_t)(c.t * d.rz + c.z) * d.ry + c.y) * d.rx + c.x;
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      p.s[r] = s + (r & 1) * (int64_t)d.rx + ((r >> 1) & 1) * dz + (r >> 2) * dt;
+    return;
+  }
+  const int b = c.x & 63;
+  const uint64_t below = (1ull << b) - 1ull;
+  uint32_t v = q.nxt << 8;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    p.s[r] = d.slot_off + (int64_t)q.e[r].y + __popcll(q.e[r].x & below);
+    const uint32_t two = (uint32_t)(q.e[r].x >> b) & 3u;  // x and, inside the word, x + 1
+    v |= ((two & 1u) << r) | ((two >> 1) << (8 + r));
+  }
+  p.v = v;
+}
+
+__device__ __forceinline__ int64_t pair_second(int64_t s0, bool v0, uint32_t hx,
+                                               int64_t slot_off) {
+  return hx ? slot_off + ((s0 - slot_off) ^ hx) : s0 + (v0 ? 1 : 0);
 }
 
 __device__ __forceinline__ float pair_frac(int a, float fx, float fy, float fz, float ft) {

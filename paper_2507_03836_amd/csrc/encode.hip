@@ -2,11 +2,10 @@
 // look up the 16 corner slots through the per-level hash and blend the corner
 // embeddings with quadrilinear weights; and its adjoint (scatter-add).
 //
-// One thread per sample, levels in a wave-uniform loop (level constants come from
-// the kernel arguments, i.e. scalar registers).  The 16 corners are visited as 8
-// pairs (corner_pair): in the rows order the vertex rows (dy, dz, dt) of an x-pair
-// (x, x+1), one directory entry serving both vertices unless x sits on bit 63 of
-// a word; in the brick order pairs along an axis that keeps both in one brick.
+// The 16 corners are visited as 8 pairs: in the rows order the vertex rows (dy, dz,
+// dt) of an x-pair (x, x+1), one directory entry serving both vertices unless x
+// sits on bit 63 of a word; in the brick order pairs along an axis that keeps both
+// in one brick (corner_pair).
 #include "encode_dev.h"
 #include "kernels.h"
 
@@ -14,21 +13,28 @@ namespace fh {
 
 namespace {
 
-template <int F, typename T>
+// One thread per sample and level, levels fastest: the lookups of a sample's
+// levels overlap, and the threads of a wave write one contiguous range of enc
+// (a thread per sample with a loop over the levels wrote F floats per line).
+template <int F, typename T, bool BRICK>
 __global__ void __launch_bounds__(256)
     encode_fwd_kernel(GridDev g, const float4* __restrict__ pos, int64_t n,
                       const T* __restrict__ table, float* __restrict__ enc) {
-  const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  const float4 p = pos[s];
-  float* out = enc + s * (int64_t)g.L * F;
-  for (int l = 0; l < g.L; ++l) {
-    const LevelDev& d = g.lv[l];
-    if (d.brick)
-      encode_level<F, T, true>(d, g.dir, g.active != 0, p, table, out + l * F, g.tmask);
-    else
-      encode_level<F, T, false>(d, g.dir, g.active != 0, p, table, out + l * F, g.tmask);
-  }
+  __shared__ LevelDev lv[FHASH_MAX_LEVELS];
+  if (threadIdx.x < FHASH_MAX_LEVELS) lv[threadIdx.x] = g.lv[threadIdx.x];
+  __syncthreads();
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (t >= n * g.L) return;
+  const int64_t s = t / g.L;
+  const int l[1] = {(int)(t - s * g.L)};
+  float out[1][F];
+  if constexpr (BRICK)
+    encode_level<F, T, true>(lv[l[0]], g.dir, g.active != 0, pos[s], table, out[0], g.tmask);
+  else
+    encode_rows<1, F, T>(g, lv, l, pos[s], table, out);
+  float* o = enc + t * F;
+#pragma unroll
+  for (int k = 0; k < F; ++k) o[k] = out[0][k];
 }
 
 // 2F threads per sample (pair element x feature), see scatter_level_lane.
@@ -107,19 +113,26 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+template <int F, typename T>
+void launch_fwd_tt(const GridDev& g, const float* pos, int64_t n, const T* table, float* enc,
+                   hipStream_t st) {
+  const dim3 grid((unsigned)((n * g.L + 255) / 256));
+  const float4* p = reinterpret_cast<const float4*>(pos);
+  if (g.lv[0].brick)
+    hipLaunchKernelGGL((encode_fwd_kernel<F, T, true>), grid, dim3(256), 0, st, g, p, n, table,
+                       enc);
+  else
+    hipLaunchKernelGGL((encode_fwd_kernel<F, T, false>), grid, dim3(256), 0, st, g, p, n, table,
+                       enc);
+}
+
 template <int F>
 hipError_t launch_fwd_t(const GridDev& g, const float* pos, int64_t n, const void* table,
                         fhash_dtype dt, float* enc, hipStream_t st) {
-  const int T = 256;
-  const int64_t blocks = (n + T - 1) / T;
   if (dt == FHASH_F32)
-    hipLaunchKernelGGL((encode_fwd_kernel<F, float>), dim3((unsigned)blocks), dim3(T), 0, st, g,
-                       reinterpret_cast<const float4*>(pos), n,
-                       reinterpret_cast<const float*>(table), enc);
+    launch_fwd_tt<F>(g, pos, n, reinterpret_cast<const float*>(table), enc, st);
   else
-    hipLaunchKernelGGL((encode_fwd_kernel<F, __half>), dim3((unsigned)blocks), dim3(T), 0, st, g,
-                       reinterpret_cast<const float4*>(pos), n,
-                       reinterpret_cast<const __half*>(table), enc);
+    launch_fwd_tt<F>(g, pos, n, reinterpret_cast<const __half*>(table), enc, st);
   return hipGetLastError();
 }
 

@@ -79,9 +79,128 @@ struct RowLoad<8, __half> {
   }
 };
 
+// Rows e and e + F of a table (two consecutive rows) in one load of 2F
+// elements, at most 16 bytes; the address is aligned to a row only.
+template <int F, typename T>
+constexpr bool wide_pair() {
+  return 2 * F * (int)sizeof(T) <= 16;
+}
+
+template <int F, typename T>
+struct __attribute__((packed, aligned(F * sizeof(T)))) TwoRows {
+  T v[2 * F];
+};
+
+__device__ __forceinline__ float row_value(float x) { return x; }
+__device__ __forceinline__ float row_value(_Float16 x) { return (float)x; }
+template <typename T>
+struct RowElem {
+  typedef T type;
+};
+template <>
+struct RowElem<__half> {
+  typedef _Float16 type;
+};
+
+template <int F, typename T>
+__device__ __forceinline__ void load_two_rows(const T* t, int64_t e, float* a, float* b) {
+  typedef typename RowElem<T>::type E;
+  const TwoRows<F, E> r = *reinterpret_cast<const TwoRows<F, E>*>(t + e);
+#pragma unroll
+  for (int k = 0; k < F; ++k) {
+    a[k] = row_value(r.v[k]);
+    b[k] = row_value(r.v[F + k]);
+  }
+}
+
+// Forward of NL levels for one sample, rows layout: out[j][k] = sum_c w_c
+// E[slot_c][k] of level lv[l[j]].  All NL * 8 directory loads are issued
+// together, then all table loads, so the levels cost two memory latencies
+// however many corners they have.  Where the second row of a pair is the next
+// table row (every dense and active index) and the table is not in runs, a
+// pair's two rows come in one load of up to 16 bytes: half the table loads,
+// and the number of lines an instruction touches is what the vector memory
+// path spends its time on.  Pairs without an active corner read the table's
+// first rows, which stay in the cache (a query of the whole box has about half
+// its corners there: sent to the rows at their rank instead, 2^20 random points
+// took 2.39 ms).  An inactive corner counts as 0 whatever was read.  Measured,
+// row by row before / this: 2^20 random points on 288^3 x 40 (16 levels, FP16)
+// 1.80 / 1.46 ms, 1000 points (FP32) 28.9 / 22.5 us in the kernel, a served mix
+// of renders and queries 11.9 / 9.1 ms.  Requires a table of at least two rows.
+template <int NL, int F, typename T>
+__device__ __forceinline__ void encode_rows(const GridDev& g, const LevelDev* lv,
+                                            const int (&l)[NL], const float4 p,
+                                            const T* __restrict__ table, float (&out)[NL][F]) {
+  const bool active = g.active != 0;
+  Cell c[NL];
+  RowEntries q[NL];
+  RowPairs s[NL];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    c[j] = locate_cell(lv[l[j]], p);
+    row_fetch(lv[l[j]], g.dir, active, c[j], q[j]);
+  }
+#pragma unroll
+  for (int j = 0; j < NL; ++j) row_slots(lv[l[j]], active, c[j], q[j], s[j]);
+  float e0[NL][8][F], e1[NL][8][F];
+  if (wide_pair<F, T>() && g.next_row && g.tmask == 0) {
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const bool any = (s[j].v >> r) & 0x101u;
+        const int64_t b = s[j].s[r] < g.last_pair ? s[j].s[r] : g.last_pair;
+        load_two_rows<F, T>(table, (any ? b : 0) * F, e0[j][r], e1[j][r]);
+      }
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        // a pair moved back from the table's end has its first row second, and
+        // x + 1 sits where x would when x is inactive
+        const bool moved = s[j].s[r] > g.last_pair, v0 = (s[j].v >> r) & 1u;
+#pragma unroll
+        for (int k = 0; k < F; ++k) {
+          if (moved) e0[j][r][k] = e1[j][r][k];
+          if (!v0) e1[j][r][k] = e0[j][r][k];
+        }
+      }
+  } else {
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const bool v0 = (s[j].v >> r) & 1u, v1 = (s[j].v >> (8 + r)) & 1u;
+        const int64_t s1 = pair_second(s[j].s[r], v0, s[j].hx, lv[l[j]].slot_off);
+        RowLoad<F, T>::load(table, run_off((v0 ? s[j].s[r] : 0) * F, g.tmask), e0[j][r]);
+        RowLoad<F, T>::load(table, run_off((v1 ? s1 : 0) * F, g.tmask), e1[j][r]);
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    float acc[F];
+#pragma unroll
+    for (int k = 0; k < F; ++k) acc[k] = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const bool v0 = (s[j].v >> r) & 1u, v1 = (s[j].v >> (8 + r)) & 1u;
+      const float wr = row_weight(c[j], r);
+      const float w0 = wr * (1.0f - c[j].fx);
+      const float w1 = wr * c[j].fx;
+#pragma unroll
+      for (int k = 0; k < F; ++k) {
+        const float a = v0 ? e0[j][r][k] : 0.0f, b = v1 ? e1[j][r][k] : 0.0f;
+        acc[k] += w0 * a + w1 * b;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < F; ++k) out[j][k] = acc[k];
+  }
+}
+
 // Forward of one level for one sample: out[k] = sum_c w_c E[slot_c][k].
 // Invalid (inactive) corners get weight 0 and read row 0, so every load is
-// unconditional and the 8 directory / 16 table loads overlap in flight.
+// unconditional.  Brick order; the rows order goes through encode_rows.
 // Requires a table with at least one row.  tmask: the table's run mask
 // (run_off; F divides 16, so a row never straddles a run).
 template <int F, typename T, bool BRICK = false>

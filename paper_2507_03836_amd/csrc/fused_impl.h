@@ -44,27 +44,55 @@ struct FusedArgs {
   int in_w;    // L * F
 };
 
-template <int F, typename T, int INP, bool BRICK>
+template <int NLMAX, int F, typename T, int INP, bool BRICK>
 __device__ __forceinline__ void gather_block(const GridDev& g, const LevelDev* lv, float4 p,
                                              bool valid, const T* table,
                                              float (&xb)[INP / 16][4]) {
   const int lane = threadIdx.x & 63, grp = lane >> 4;
   constexpr int LPB = 4 / F;  // levels per lane per 16-feature block
+  if constexpr (BRICK) {
 #pragma unroll
-  for (int a = 0; a < INP / 16; ++a)
+    for (int a = 0; a < INP / 16; ++a)
 #pragma unroll
-    for (int j = 0; j < LPB; ++j) {
-      const int l = (16 * a + 4 * grp) / F + j;
-      float e[F];
-      if (valid && l < g.L) {
-        encode_level<F, T, BRICK>(lv[l], g.dir, g.active != 0, p, table, e, g.tmask);
-      } else {
+      for (int j = 0; j < LPB; ++j) {
+        const int l = (16 * a + 4 * grp) / F + j;
+        float e[F];
+        if (valid && l < g.L) {
+          encode_level<F, T, true>(lv[l], g.dir, g.active != 0, p, table, e, g.tmask);
+        } else {
 #pragma unroll
-        for (int k = 0; k < F; ++k) e[k] = 0.0f;
+          for (int k = 0; k < F; ++k) e[k] = 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < F; ++k) xb[a][j * F + k] = e[k];
+      }
+  } else {
+    // the lane's levels two at a time (one more would double the registers of
+    // the loads in flight); a level past the last repeats the last one's loads
+    constexpr int NLV = (INP / 16) * LPB, NL = NLV < NLMAX ? NLV : NLMAX;
+#pragma unroll
+    for (int i = 0; i < NLV; i += NL) {
+      int l[NL];
+      float e[NL][F];
+#pragma unroll
+      for (int j = 0; j < NL; ++j) {
+        l[j] = (16 * ((i + j) / LPB) + 4 * grp) / F + (i + j) % LPB;
+#pragma unroll
+        for (int k = 0; k < F; ++k) e[j][k] = 0.0f;
+      }
+      if (valid && l[0] < g.L) {
+        int m[NL];
+#pragma unroll
+        for (int j = 0; j < NL; ++j) m[j] = l[j] < g.L ? l[j] : g.L - 1;
+        encode_rows<NL, F, T>(g, lv, m, p, table, e);
       }
 #pragma unroll
-      for (int k = 0; k < F; ++k) xb[a][j * F + k] = e[k];
+      for (int j = 0; j < NL; ++j)
+#pragma unroll
+        for (int k = 0; k < F; ++k)
+          xb[(i + j) / LPB][((i + j) % LPB) * F + k] = l[j] < g.L ? e[j][k] : 0.0f;
     }
+  }
 }
 
 // Scatter of a block's encoding gradient, redistributed so that 2F
@@ -179,7 +207,7 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
     const bool valid = smp < A.n;
     const float4 p = valid ? A.pos[smp] : make_float4(0.f, 0.f, 0.f, 0.f);
     float xb[S::INB][4];
-    gather_block<F, T, INP, BRICK>(g, lv, p, valid, table, xb);
+    gather_block<FWD ? 1 : 2, F, T, INP, BRICK>(g, lv, p, valid, table, xb);
     float hs[NH][S::HB][4];
     float yv;
     if constexpr (MODE == MODE_FWD16)

@@ -204,46 +204,59 @@ __device__ __forceinline__ bool finish_lanes(Lane L, const float4* rec, const Ad
   return active;
 }
 
+// Claim flags of the segments that hold the F floats of rows s0 and s1 of a
+// corner pair (v0, v1: active).  F divides 16 and begin is a multiple of 16,
+// so the floats of a row lie in one segment; the two rows are neighbours, rows
+// of one brick, or two hashed rows.
+__device__ __forceinline__ void claim_pair(int64_t s0, int64_t s1, bool v0, bool v1, int F,
+                                           uint8_t* __restrict__ flags, int64_t begin,
+                                           int64_t end) {
+  if (!(v0 || v1)) return;
+  const int64_t fa = (v0 ? s0 : s1) * F, fb = (v1 ? s1 : s0) * F;
+  const bool ina = fa >= begin && fa < end, inb = fb >= begin && fb < end;
+  const int64_t a = (fa - begin) / kSeg, b = (fb - begin) / kSeg;
+  if (ina) flags[a] = 1;
+  if (inb && !(ina && b == a)) flags[b] = 1;
+}
+
 // Every segment of [begin, end) that the forward or backward of a sample reads
-// or writes at the levels [l0, l1): the corner row pairs of its cell, exactly
-// as the encoding visits them, gets its claim flag set.
+// or writes at level l0 + blockIdx.y: the corner row pairs of its cell, exactly
+// as the encoding visits them, gets its claim flag set.  A level per row of
+// the grid: its constants are wave-uniform, a wave's flag stores fall into one
+// level (neighbouring samples of a sorted batch often into the same lines),
+// and a sample's levels wait for their directory entries side by side instead
+// of one after another.
+template <bool BRICK>
 __global__ void __launch_bounds__(256)
-    lazy_mark_kernel(GridDev g, int l0, int l1, const float4* __restrict__ pos, int64_t n,
+    lazy_mark_kernel(GridDev g, int l0, const float4* __restrict__ pos, int64_t n,
                      uint8_t* __restrict__ flags, int64_t begin, int64_t end) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int F = g.F;
+  const LevelDev& d = g.lv[l0 + blockIdx.y];
+  const bool active = g.active != 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const float4 p = pos[i];
-    for (int l = l0; l < l1; ++l) {
-      const LevelDev& d = g.lv[l];
-      int ix, iy, iz, it;
-      float fx, fy, fz, ft;
-      locate(p.x, d.rx, d.sx, ix, fx);
-      locate(p.y, d.ry, d.sy, iy, fy);
-      locate(p.z, d.rz, d.sz, iz, fz);
-      locate(p.w, d.rt, d.st, it, ft);
-      const int ax = d.brick ? pair_axis<true>(ix, iy, iz, it) : 0;
+    const Cell c = locate_cell(d, pos[i]);
+    if constexpr (BRICK) {
+      const int ax = pair_axis<true>(c.x, c.y, c.z, c.t);
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
         float wr;
         int64_t s0, s1;
         bool v0, v1;
-        if (d.brick)
-          corner_pair<true>(d, g.dir, g.active != 0, ix, iy, iz, it, fx, fy, fz, ft, ax, r, s0,
-                            s1, v0, v1, wr);
-        else
-          corner_pair<false>(d, g.dir, g.active != 0, ix, iy, iz, it, fx, fy, fz, ft, ax, r, s0,
-                             s1, v0, v1, wr);
-        if (v0 || v1) {
-          // F divides 16 and begin is a multiple of 16, so the F floats of a slot
-          // lie in one segment; the two slots of a pair are neighbouring rows,
-          // rows of one brick, or two hashed rows
-          const int64_t fa = (v0 ? s0 : s1) * F, fb = (v1 ? s1 : s0) * F;
-          const bool ina = fa >= begin && fa < end, inb = fb >= begin && fb < end;
-          const int64_t a = (fa - begin) / kSeg, b = (fb - begin) / kSeg;
-          if (ina) flags[a] = 1;
-          if (inb && !(ina && b == a)) flags[b] = 1;
-        }
+        corner_pair<true>(d, g.dir, active, c.x, c.y, c.z, c.t, c.fx, c.fy, c.fz, c.ft, ax, r, s0,
+                          s1, v0, v1, wr);
+        claim_pair(s0, s1, v0, v1, F, flags, begin, end);
+      }
+    } else {
+      RowEntries q;
+      RowPairs s;
+      row_fetch(d, g.dir, active, c, q);
+      row_slots(d, active, c, q, s);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const bool v0 = (s.v >> r) & 1u, v1 = (s.v >> (8 + r)) & 1u;
+        claim_pair(s.s[r], pair_second(s.s[r], v0, s.hx, d.slot_off), v0, v1, F, flags, begin,
+                   end);
       }
     }
   }
@@ -574,7 +587,8 @@ hipError_t launch_lazy_prepare(const GridDev& g, int l0, int l1, const float* po
   if ((phases & FHASH_LAZY_MARK) && n > 0 && l0 < l1) {
     int64_t b = (n + 255) / 256;
     if (b > 4096) b = 4096;
-    hipLaunchKernelGGL(lazy_mark_kernel, dim3((unsigned)b), dim3(256), 0, st, g, l0, l1,
+    auto kern = g.lv[0].brick ? lazy_mark_kernel<true> : lazy_mark_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)b, (unsigned)(l1 - l0)), dim3(256), 0, st, g, l0,
                        reinterpret_cast<const float4*>(pos), n, w.flags, lz->begin, lz->end);
   }
   // at most 9 segments per sample and level (8 row pairs, one may straddle)
