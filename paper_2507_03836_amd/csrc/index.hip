@@ -1,13 +1,23 @@
-// Index build: voxel feature mask -> per-level active cells -> active vertices ->
-// rank directory (the collision-free per-level hash, Sec. 3.2.3 / Sec. 3.1).
+// Index build: voxel feature mask -> per-level active vertices -> rank directory
+// (the collision-free per-level hash, Sec. 3.2.3 / Sec. 3.1).
 //
-// A level's active cells are found with separable OR-reductions of the bit mask
-// along t, z, y (whole 64-bit words) and a final bit-range test along x; the
-// active vertices are the separable 1-step dilation of the active cells along
-// t, z, y, x.  The directory stores, for every 64-vertex word of a row-padded
-// vertex bitmap, the bits and the number of active vertices before the word
-// (exclusive prefix sum of popcounts in F-Hash linearisation order).  Row
-// padding bits are zero, so ranks equal ranks in the unpadded order.
+// Voxel i of a dimension sits at u = i (R-1)/(S-1) on a level, a cell is active
+// iff its closed box contains a masked voxel, and a vertex iff one of its cells
+// is: iff some masked voxel lies within one vertex spacing of it along every
+// axis.  That is separable, so a level's vertex bits come from one OR over
+// voxel ranges per axis: along y (usually the axis a level shrinks most, so the
+// later passes have the least to read), along z and t (vertex v = cell v-1 OR
+// cell v, each voxel read once per thread), and along x inside the words.
+//
+// The mask is first transposed to [t][z][word][y], the store order of the
+// directory, so that neighbouring threads of every pass hold neighbouring y:
+// coalesced loads and stores, and the word index and the x ranges of its 64
+// vertices are the same in every lane (scalar arithmetic).  The directory
+// stores, for every 64-vertex word of a row-padded vertex bitmap, the bits and
+// the number of active vertices before the word (exclusive prefix sum of
+// popcounts in F-Hash linearisation order).  Row padding bits are zero, so ranks
+// equal ranks in the unpadded order.  Levels small enough to share the
+// workspace of the largest go through each pass in one launch.
 #include <algorithm>
 
 #include "common.h"
@@ -17,145 +27,156 @@ namespace fh {
 
 namespace {
 
-__device__ __forceinline__ void voxel_range(int64_t c, int64_t S, int64_t R, int64_t& lo,
-                                            int64_t& hi) {
-  // Voxels i with c <= i(R-1)/(S-1) <= c+1 (closed cell box).
-  const int64_t d = S - 1, r = R - 1;
-  lo = (c * d + r - 1) / r;
-  hi = ((c + 1) * d) / r;
-  if (hi > S - 1) hi = S - 1;
+// Voxels i with c <= i(R-1)/(S-1) <= c+1 (closed cell box): ceil(c (S-1)/(R-1))
+// .. floor((c+1)(S-1)/(R-1)).
+// (S - 1) R below 2^31 (every volume of thousands of voxels a side): 32-bit
+// divisions, a quarter of the 64-bit ones' instructions.
+__device__ __forceinline__ int64_t range_lo(int64_t c, int64_t S, int64_t R) {
+  if ((S - 1) * R < ((int64_t)1 << 31))
+    return ((uint32_t)c * (uint32_t)(S - 1) + (uint32_t)(R - 2)) / (uint32_t)(R - 1);
+  return (c * (S - 1) + R - 2) / (R - 1);
+}
+__device__ __forceinline__ int64_t range_hi(int64_t c, int64_t S, int64_t R) {
+  const int64_t hi = (S - 1) * R < ((int64_t)1 << 31)
+                         ? (uint32_t)(c + 1) * (uint32_t)(S - 1) / (uint32_t)(R - 1)
+                         : ((c + 1) * (S - 1)) / (R - 1);
+  return hi > S - 1 ? S - 1 : hi;
 }
 
-// out[o][c][q] = OR over voxels s of cell c of in[o][s][q].
-__global__ void or_reduce_axis_kernel(const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
-                                      int64_t outer, int64_t S, int64_t C, int64_t inner,
-                                      int64_t R) {
-  const int64_t total = outer * C * inner;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t q = e % inner;
-    const int64_t c = (e / inner) % C;
-    const int64_t o = e / (inner * C);
-    int64_t lo, hi;
-    voxel_range(c, S, R, lo, hi);
-    uint64_t acc = 0;
-    const uint64_t* src = in + (o * S) * inner + q;
-    for (int64_t s = lo; s <= hi; ++s) acc |= src[s * inner];
-    out[e] = acc;
+// floor(k (S-1)/(R-1)) for k, k+1, ... without a division per step.
+struct Steps {
+  int32_t q, dq, r, dr, n;  // S <= 2^31 and k < R: every quotient fits
+  __device__ __forceinline__ Steps(int64_t k, int64_t S, int64_t R) {
+    n = (int32_t)(R - 1);
+    const int64_t p = k * (S - 1);
+    q = (int32_t)(p / n);
+    r = (int32_t)(p - (int64_t)q * n);
+    dq = (int32_t)((S - 1) / n);
+    dr = (int32_t)((S - 1) - (int64_t)dq * n);
+  }
+  __device__ __forceinline__ void next() {
+    q += dq;
+    r += dr;
+    if (r >= n) {
+      r -= n;
+      ++q;
+    }
+  }
+};
+
+// One level of a launch: vertex counts, words per vertex row, and where its
+// part of each workspace array begins (64-bit words; row counts; row blocks).
+struct LevelBuild {
+  int32_t rx, ry, rz, rt, wv, y0;  // y0: ry of the group's levels before this one
+  int64_t a, b, c, bits;
+  int64_t row, blk, dir;
+};
+constexpr int kMaxGroup = FHASH_MAX_LEVELS;
+struct GroupBuild {
+  LevelBuild lv[kMaxGroup];
+  int64_t Sx, Sy, Sz, St, Wm;
+};
+
+// Mask rows [t][z][y][w] -> [t][z][w][y], 64 y by up to 32 words at a time
+// through LDS, so that both sides are read and written in runs.
+constexpr int kTileW = 32;
+__global__ void __launch_bounds__(256)
+    transpose_kernel(const uint64_t* __restrict__ in, uint64_t* __restrict__ out, int64_t slabs,
+                     int64_t Sy, int64_t W) {
+  __shared__ uint64_t tile[kTileW][65];
+  const int64_t ty = (Sy + 63) / 64, tw = (W + kTileW - 1) / kTileW, tiles = slabs * ty * tw;
+  for (int64_t e = blockIdx.x; e < tiles; e += gridDim.x) {
+    const int64_t slab = e / (ty * tw), rest = e - slab * ty * tw;
+    const int64_t y0 = rest / tw * 64, w0 = rest % tw * kTileW;
+    const int ny = Sy - y0 < 64 ? (int)(Sy - y0) : 64;
+    const int nw = W - w0 < kTileW ? (int)(W - w0) : kTileW;
+    const uint64_t* src = in + slab * Sy * W + y0 * W + w0;
+    uint64_t* dst = out + slab * Sy * W + w0 * Sy + y0;
+    for (int i = threadIdx.x; i < ny * nw; i += 256) {
+      const int y = i / nw, w = i - y * nw;
+      tile[w][y] = src[y * W + w];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 64 * nw; i += 256)
+      if ((i & 63) < ny) dst[(i >> 6) * Sy + (i & 63)] = tile[i >> 6][i & 63];
+    __syncthreads();
   }
 }
 
-// Cell bits along x: bit cx of row r = any voxel bit in the x-range of cell cx.
-__global__ void cells_x_kernel(const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
-                               int64_t rows, int64_t Wm, int64_t Wc, int64_t Sx, int64_t Rx) {
-  const int64_t total = rows * Wc;
-  const int64_t Cx = Rx - 1;
+// out[o][v][q] = OR over the voxels s of cells v-1 and v of in[o][s][q]: a
+// thread walks `per` vertices of one (o, q), so a voxel is read once (twice on
+// a cell face).  inner: words that share an (o, s).  A walk is a chain of
+// loads, so lines are cut into chunks of vertices (at least 4, each chunk reads
+// one cell of its neighbour's again) until 2^20 threads share the work: the z
+// pass of the 480x720x120x24 volume's levels took 427 us at 2^18 and 332 us so.
+constexpr int64_t kLineThreads = 1 << 20;
+__device__ __forceinline__ void or_axis(const uint64_t* __restrict__ in,
+                                        uint64_t* __restrict__ out, int64_t outer, int64_t S,
+                                        int64_t R, int64_t inner) {
+  // vertices per thread: fewer where (outer, inner) alone leaves the chip idle
+  const int64_t lines = outer * inner;
+  int64_t chunks = lines >= kLineThreads ? 1 : (kLineThreads + lines - 1) / lines;
+  if (chunks > (R + 3) / 4) chunks = (R + 3) / 4;
+  const int64_t per = (R + chunks - 1) / chunks, total = lines * chunks;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t w = e % Wc, r = e / Wc;
-    const uint64_t* row = in + r * Wm;
-    uint64_t bits = 0;
-    for (int b = 0; b < 64; ++b) {
-      const int64_t cx = w * 64 + b;
-      if (cx >= Cx) break;
-      int64_t lo, hi;
-      voxel_range(cx, Sx, Rx, lo, hi);
-      bool any = false;
-      for (int64_t wi = lo >> 6; wi <= (hi >> 6) && !any; ++wi) {
-        uint64_t m = row[wi];
-        const int64_t b0 = wi * 64;
-        if (lo > b0) m &= ~0ull << (lo - b0);
-        if (hi < b0 + 63) m &= (1ull << (hi - b0 + 1)) - 1ull;
-        any = m != 0;
+    const int64_t q = e % inner, rest = e / inner;
+    const int64_t v0 = (rest % chunks) * per, o = rest / chunks;
+    const int64_t v1 = v0 + per < R ? v0 + per : R;
+    const uint64_t* src = in + o * S * inner + q;
+    uint64_t* dst = out + o * R * inner + q;
+    int64_t c = v0 > 0 ? v0 - 1 : 0;
+    Steps top(c, S, R);
+    int64_t lo = top.q + (top.r > 0 ? 1 : 0);
+    uint64_t prev = 0;
+    for (; c < v1; ++c) {
+      uint64_t cell = 0;
+      if (c < R - 1) {
+        top.next();
+        const int64_t hi = top.q < S - 1 ? top.q : S - 1;
+#pragma unroll 4
+        for (int64_t s = lo; s <= hi; ++s) cell |= src[s * inner];
+        lo = top.q + (top.r > 0 ? 1 : 0);
       }
-      if (any) bits |= 1ull << b;
+      if (c >= v0) dst[c * inner] = prev | cell;
+      prev = cell;
     }
-    out[e] = bits;
   }
 }
 
-// Vertex dilation along one axis: out[o][v][q] = in[o][v-1][q] | in[o][v][q],
-// where in has C = R-1 cells along the axis and out has R vertices.
-__global__ void dilate_axis_kernel(const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
-                                   int64_t outer, int64_t C, int64_t inner) {
-  const int64_t R = C + 1;
-  const int64_t total = outer * R * inner;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t q = e % inner;
-    const int64_t v = (e / inner) % R;
-    const int64_t o = e / (inner * R);
-    const uint64_t* src = in + o * C * inner + q;
-    uint64_t acc = 0;
-    if (v < C) acc |= src[v * inner];
-    if (v > 0) acc |= src[(v - 1) * inner];
-    out[e] = acc;
-  }
-}
-
-// Vertex bits along x (vertex x active iff cell x or cell x-1 active), written
-// into the directory's bit words.
-__global__ void vert_x_kernel(const uint64_t* __restrict__ in, ulonglong2* __restrict__ dir,
-                              int64_t rows, int64_t Wc, int64_t Wv) {
-  const int64_t total = rows * Wv;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t w = e % Wv, r = e / Wv;
-    const uint64_t* row = in + r * Wc;
-    const uint64_t cur = (w < Wc) ? row[w] : 0ull;
-    const uint64_t prev = (w > 0 && w - 1 < Wc) ? row[w - 1] : 0ull;
-    ulonglong2 ent;
-    ent.x = cur | (cur << 1) | (prev >> 63);
-    ent.y = 0;
-    dir[e] = ent;
-  }
-}
-
-// Store order of the directory: the entries of one x word for all y of a
-// (t, z) row block are adjacent, index ((t*Rz + z)*Wv + w)*Ry + y, so the
-// y and y+1 rows of a cell read neighbouring 16-byte entries (one line).
-// Ranks are computed in F-Hash order first (row-major, src) and then moved.
-__global__ void dir_interleave_kernel(const ulonglong2* __restrict__ src,
-                                      ulonglong2* __restrict__ dst, int64_t rows, int64_t ry,
-                                      int64_t wv) {
-  const int64_t total = rows * wv;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t w = e % wv, row = e / wv;
-    const int64_t tz = row / ry, y = row % ry;
-    dst[(tz * wv + w) * ry + y] = src[e];
-  }
-}
-
-// Brick order (layout FHASH_LAYOUT_BRICKS): word w of brick row (bt, bz, by)
-// holds bricks bx = 4w .. 4w+3, brick q at bits 16q .. 16q+15, vertex inner
-// index (x%2) | (y%2)<<1 | (z%2)<<2 | (t%2)<<3.  Built from the row-major
-// vertex bits (rows (t, z, y) of wv words): the 8 x bits 8w .. 8w+7 of each of
-// the brick row's 8 vertex rows lie in one row word.  Output in brick-linear
-// order (((bt*Bz + bz)*By + by)*Wb + w), ranks still to be written.
-__global__ void brickify_kernel(const ulonglong2* __restrict__ rows, ulonglong2* __restrict__ out,
-                                int64_t rx, int64_t ry, int64_t rz, int64_t rt, int64_t wv,
-                                int64_t wb, int64_t by_n, int64_t bz_n, int64_t total) {
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t w = e % wb, row = e / wb;
-    const int64_t by = row % by_n, bz = (row / by_n) % bz_n, bt = row / (by_n * bz_n);
-    uint64_t bits = 0;
-    for (int c = 0; c < 8; ++c) {  // (y%2, z%2, t%2) of the vertex row
-      const int64_t y = 2 * by + (c & 1), z = 2 * bz + ((c >> 1) & 1), t = 2 * bt + (c >> 2);
-      if (y >= ry || z >= rz || t >= rt) continue;
-      const int64_t x0 = 8 * w;  // x bits 8w .. 8w+7 (x >= rx reads the row's zero padding)
-      if (x0 >= rx) continue;
-      const uint64_t xb = (rows[((t * rz + z) * ry + y) * wv + (x0 >> 6)].x >> (x0 & 63)) & 0xFFull;
-      for (int q = 0; q < 4; ++q)
-        for (int ix = 0; ix < 2; ++ix)
-          if ((xb >> (2 * q + ix)) & 1ull) bits |= 1ull << (16 * q + (ix | (c << 1)));
+// Along y: [line][Sy] -> [line][ry] for every level of the group, line = (t, z,
+// word).  A workgroup takes a line through all the levels (items: their
+// vertices, numbered through), so that it is read from memory once.
+__global__ void __launch_bounds__(256)
+    or_y_kernel(GroupBuild G, int32_t items, const uint64_t* __restrict__ mask,
+                uint64_t* __restrict__ A) {
+  const int64_t lines = G.St * G.Sz * G.Wm;
+  for (int64_t line = blockIdx.x; line < lines; line += gridDim.x) {
+    const uint64_t* src = mask + line * G.Sy;
+    int j = 0;
+    for (int32_t e = threadIdx.x; e < items; e += 256) {
+      while (e >= G.lv[j].y0 + G.lv[j].ry) ++j;
+      const int32_t R = G.lv[j].ry, v = e - G.lv[j].y0;
+      const int64_t lo = v > 0 ? range_lo(v - 1, G.Sy, R) : 0;
+      const int64_t hi = v < R - 1 ? range_hi(v, G.Sy, R) : G.Sy - 1;
+      uint64_t acc = 0;
+#pragma unroll 4
+      for (int64_t s = lo; s <= hi; ++s) acc |= src[s];
+      A[G.lv[j].a + line * R + v] = acc;
     }
-    ulonglong2 ent;
-    ent.x = bits;
-    ent.y = 0;
-    out[e] = ent;
   }
+}
+
+__global__ void __launch_bounds__(256)
+    or_z_kernel(GroupBuild G, const uint64_t* __restrict__ A, uint64_t* __restrict__ B) {
+  const LevelBuild& d = G.lv[blockIdx.y];
+  or_axis(A + d.a, B + d.b, G.St, G.Sz, d.rz, G.Wm * d.ry);
+}
+
+__global__ void __launch_bounds__(256)
+    or_t_kernel(GroupBuild G, const uint64_t* __restrict__ B, uint64_t* __restrict__ C) {
+  const LevelBuild& d = G.lv[blockIdx.y];
+  or_axis(B + d.b, C + d.c, 1, G.St, d.rt, d.rz * G.Wm * d.ry);
 }
 
 constexpr int kScanThreads = 256;
@@ -190,6 +211,162 @@ __device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t* s
   return res;
 }
 
+// Along x and the row counts: a workgroup takes kRows vertex rows (t, z, y), a
+// lane per row, and each of its waves every fourth word, so that a wave's word
+// and the voxel ranges of its vertices are the same in every lane.  Output word
+// w holds vertices 64w .. 64w + 63; a vertex is set iff the row has a voxel bit
+// in its range.  Writes the bits in [tz][w][y] order, each row's count, and the
+// block's total.
+constexpr int kRows = 64;
+__global__ void __launch_bounds__(256)
+    rows_kernel(GroupBuild G, const uint64_t* __restrict__ C, uint64_t* __restrict__ bits,
+                uint32_t* __restrict__ row_count, uint64_t* __restrict__ partial) {
+  __shared__ uint32_t sh[4][kRows];
+  const LevelBuild& d = G.lv[blockIdx.y];
+  const int64_t rows = (int64_t)d.rt * d.rz * d.ry;
+  if (blockIdx.x * (int64_t)kRows >= rows) return;  // uniform: a smaller level
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t row = blockIdx.x * (int64_t)kRows + lane;
+  const bool valid = row < rows;
+  const int64_t mine = valid ? row : rows - 1;  // every lane stays with its wave
+  const int64_t tz = mine / d.ry, y = mine - tz * d.ry;
+  const uint64_t* src = C + d.c + tz * G.Wm * d.ry + y;
+  uint64_t* dst = bits + d.bits + tz * d.wv * d.ry + y;
+  const int32_t Wm = (int32_t)G.Wm;
+  uint32_t count = 0;
+  for (int32_t w = wid; w < d.wv; w += 4) {
+    uint64_t o = 0;
+    const int nb = d.rx - 64 * w < 64 ? d.rx - 64 * w : 64;
+    if (d.rx == G.Sx) {
+      // one vertex per voxel: the voxel, its left and its right neighbour
+      const uint64_t prev = w > 0 ? src[(int64_t)(w - 1) * d.ry] : 0ull;
+      const uint64_t cur = src[(int64_t)w * d.ry];
+      const uint64_t next = w + 1 < Wm ? src[(int64_t)(w + 1) * d.ry] : 0ull;
+      o = cur | (cur << 1) | (prev >> 63) | (cur >> 1) | (next << 63);
+      if (nb < 64) o &= (1ull << nb) - 1ull;
+    } else {
+      // voxels lo .. hi of vertex v (cells v - 1 and v): lane b works out those
+      // of vertex 64 w + b, from where they are read back as scalars
+      const int64_t v = 64 * (int64_t)w + lane;
+      const int32_t lo_b = v > 0 ? (int32_t)range_lo(v - 1, G.Sx, d.rx) : 0;
+      const int32_t hi_b = (int32_t)(v < d.rx - 1 ? range_hi(v, G.Sx, d.rx) : G.Sx - 1);
+      int32_t have = -2;  // the word held in cur; prev holds the one before it
+      uint64_t prev = 0, cur = 0;
+      for (int b = 0; b < nb; ++b) {
+        const int32_t lo = __builtin_amdgcn_readlane(lo_b, b);
+        const int32_t hi = __builtin_amdgcn_readlane(hi_b, b);
+        if (lo > hi) continue;  // no voxel near this vertex (a level finer than the volume)
+        const int32_t w0 = lo >> 6, w1 = hi >> 6;
+        if (w1 != have) {
+          prev = w1 == have + 1 ? cur : w1 > 0 ? src[(int64_t)(w1 - 1) * d.ry] : 0ull;
+          cur = src[(int64_t)w1 * d.ry];
+          have = w1;
+        }
+        const uint64_t from = ~0ull << (lo & 63), upto = ~0ull >> (63 - (hi & 63));
+        uint64_t any;
+        if (w0 == w1) {
+          any = cur & (from & upto);
+        } else {
+          any = cur & upto;
+          if (w0 == w1 - 1) {
+            any |= prev & from;
+          } else {
+            any |= prev | (src[(int64_t)w0 * d.ry] & from);
+            for (int32_t wi = w0 + 1; wi < w1 - 1; ++wi) any |= src[(int64_t)wi * d.ry];
+          }
+        }
+        o |= (any != 0 ? 1ull : 0ull) << b;
+      }
+    }
+    if (valid) dst[(int64_t)w * d.ry] = o;
+    count += valid ? __popcll(o) : 0;
+  }
+  sh[wid][lane] = count;
+  __syncthreads();
+  if (wid == 0) {
+    const uint32_t c = sh[0][lane] + sh[1][lane] + sh[2][lane] + sh[3][lane];
+    if (valid) row_count[d.row + row] = c;
+    uint64_t total = c;
+    for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
+    if (lane == 0) partial[d.blk + blockIdx.x] = total;
+  }
+}
+
+// The directory: {bits, active vertices before the word} of every word, from
+// the row counts' prefix sum; kScanThreads rows per workgroup (kRows divides it).
+__global__ void __launch_bounds__(kScanThreads)
+    entries_kernel(GroupBuild G, const uint64_t* __restrict__ bits,
+                   const uint32_t* __restrict__ row_count, const uint64_t* __restrict__ partial,
+                   ulonglong2* __restrict__ dir) {
+  __shared__ uint64_t sh[17];
+  const LevelBuild& d = G.lv[blockIdx.y];
+  const int64_t rows = (int64_t)d.rt * d.rz * d.ry;
+  if (blockIdx.x * (int64_t)kScanThreads >= rows) return;  // uniform: a smaller level
+  const int64_t row = blockIdx.x * (int64_t)kScanThreads + threadIdx.x;
+  const bool valid = row < rows;
+  uint64_t total;
+  uint64_t run = block_exclusive_scan(valid ? row_count[d.row + row] : 0u, sh, total) +
+                 partial[d.blk + blockIdx.x * (int64_t)(kScanThreads / kRows)];
+  if (!valid) return;
+  const int64_t tz = row / d.ry, y = row - tz * d.ry;
+  const int64_t at = tz * d.wv * d.ry + y;
+  for (int64_t w = 0; w < d.wv; ++w) {
+    const uint64_t o = bits[d.bits + at + w * d.ry];
+    ulonglong2 ent;
+    ent.x = o;
+    ent.y = run;
+    dir[d.dir + at + w * d.ry] = ent;
+    run += __popcll(o);
+  }
+}
+
+// Store order of a brick directory: the entries of one word index for all
+// brick rows of a (t, z) block are adjacent, so that the brick rows y and y+1
+// of a cell read neighbouring entries.  Ranks are computed row-major first.
+__global__ void dir_interleave_kernel(const ulonglong2* __restrict__ src,
+                                      ulonglong2* __restrict__ dst, int64_t rows, int64_t ry,
+                                      int64_t wv) {
+  const int64_t total = rows * wv;
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
+       e += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t w = e % wv, row = e / wv;
+    const int64_t tz = row / ry, y = row % ry;
+    dst[(tz * wv + w) * ry + y] = src[e];
+  }
+}
+
+// Brick order (layout FHASH_LAYOUT_BRICKS): word w of brick row (bt, bz, by)
+// holds bricks bx = 4w .. 4w+3, brick q at bits 16q .. 16q+15, vertex inner
+// index (x%2) | (y%2)<<1 | (z%2)<<2 | (t%2)<<3.  Built from the vertex bits in
+// [tz][word][y] order: the 8 x bits 8w .. 8w+7 of each of the brick row's 8
+// vertex rows lie in one word.  Output in brick-linear
+// order (((bt*Bz + bz)*By + by)*Wb + w), ranks still to be written.
+__global__ void brickify_kernel(const uint64_t* __restrict__ rows, ulonglong2* __restrict__ out,
+                                int64_t rx, int64_t ry, int64_t rz, int64_t rt, int64_t wv,
+                                int64_t wb, int64_t by_n, int64_t bz_n, int64_t total) {
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
+       e += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t w = e % wb, row = e / wb;
+    const int64_t by = row % by_n, bz = (row / by_n) % bz_n, bt = row / (by_n * bz_n);
+    uint64_t bits = 0;
+    for (int c = 0; c < 8; ++c) {  // (y%2, z%2, t%2) of the vertex row
+      const int64_t y = 2 * by + (c & 1), z = 2 * bz + ((c >> 1) & 1), t = 2 * bt + (c >> 2);
+      if (y >= ry || z >= rz || t >= rt) continue;
+      const int64_t x0 = 8 * w;  // x bits 8w .. 8w+7 (x >= rx reads the row's zero padding)
+      if (x0 >= rx) continue;
+      const uint64_t xb = (rows[((t * rz + z) * wv + (x0 >> 6)) * ry + y] >> (x0 & 63)) & 0xFFull;
+      for (int q = 0; q < 4; ++q)
+        for (int ix = 0; ix < 2; ++ix)
+          if ((xb >> (2 * q + ix)) & 1ull) bits |= 1ull << (16 * q + (ix | (c << 1)));
+    }
+    ulonglong2 ent;
+    ent.x = bits;
+    ent.y = 0;
+    out[e] = ent;
+  }
+}
+
 __global__ void __launch_bounds__(kScanThreads)
     popc_block_sums_kernel(const ulonglong2* __restrict__ dir, int64_t words,
                            uint64_t* __restrict__ partial) {
@@ -203,24 +380,43 @@ __global__ void __launch_bounds__(kScanThreads)
   if (threadIdx.x == 0) partial[blockIdx.x] = total;
 }
 
-// Exclusive scan of the block partials in one workgroup; *count = total.
+// Exclusive scan of the block partials of one level (blockIdx.x) in one
+// workgroup: 4 per thread and round; count = total.
+__device__ __forceinline__ void scan_partials(uint64_t* __restrict__ partial, int64_t nb,
+                                              uint64_t* __restrict__ count) {
+  __shared__ uint64_t sh[17];
+  uint64_t carry = 0;
+  for (int64_t r0 = 0; r0 < nb; r0 += 4096) {
+    const int64_t i0 = r0 + 4 * (int64_t)threadIdx.x;
+    uint64_t v[4], s = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = i0 + k < nb ? partial[i0 + k] : 0ull;
+      s += v[k];
+    }
+    uint64_t total;
+    uint64_t run = carry + block_exclusive_scan(s, sh, total);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i0 + k < nb) {
+        partial[i0 + k] = run;
+        run += v[k];
+      }
+    carry += total;
+  }
+  if (threadIdx.x == 0) *count = carry;
+}
+
 __global__ void __launch_bounds__(1024)
     scan_partials_kernel(uint64_t* __restrict__ partial, int64_t nb, uint64_t* __restrict__ count) {
-  __shared__ uint64_t sh[17];
-  const int64_t per = (nb + blockDim.x - 1) / blockDim.x;
-  const int64_t b0 = threadIdx.x * per;
-  uint64_t s = 0;
-  for (int64_t i = 0; i < per; ++i)
-    if (b0 + i < nb) s += partial[b0 + i];
-  uint64_t total;
-  uint64_t run = block_exclusive_scan(s, sh, total);
-  for (int64_t i = 0; i < per; ++i)
-    if (b0 + i < nb) {
-      uint64_t t = partial[b0 + i];
-      partial[b0 + i] = run;
-      run += t;
-    }
-  if (threadIdx.x == 0) *count = total;
+  scan_partials(partial, nb, count);
+}
+
+__global__ void __launch_bounds__(1024)
+    scan_rows_kernel(GroupBuild G, uint64_t* __restrict__ partial, uint64_t* __restrict__ counts) {
+  const LevelBuild& d = G.lv[blockIdx.x];
+  const int64_t rows = (int64_t)d.rt * d.rz * d.ry;
+  scan_partials(partial + d.blk, (rows + kRows - 1) / kRows, counts + blockIdx.x);
 }
 
 __global__ void __launch_bounds__(kScanThreads)
@@ -250,31 +446,23 @@ inline int grid_for(int64_t total, int threads) {
   return (int)b;
 }
 
+// Sizes of one level's parts of the workspace: a, b, c and bits in words (the
+// outputs of the passes along y, z, t and x), rows, row blocks, and the brick
+// directory.
 struct LevelSizes {
-  int64_t Ct, Cz, Cy, Cx, Wm, Wc, Wv;
-  int64_t A, B, Cb, cell, D1, D2, D3, words, nb;
+  int64_t a, b, c, bits, rows, blk;
   int64_t Bx, By, Bz, Bt, Wb, bwords, bnb;  // brick layout
 };
 
 LevelSizes level_sizes(const int32_t* r, const int64_t* dims) {
   LevelSizes s;
-  const int64_t Sx = dims[0], Sy = dims[1], Sz = dims[2];
-  s.Cx = r[0] - 1;
-  s.Cy = r[1] - 1;
-  s.Cz = r[2] - 1;
-  s.Ct = r[3] - 1;
-  s.Wm = (Sx + 63) / 64;
-  s.Wc = (s.Cx + 63) / 64;
-  s.Wv = ((int64_t)r[0] + 63) / 64;
-  s.A = s.Ct * Sz * Sy * s.Wm;
-  s.B = s.Ct * s.Cz * Sy * s.Wm;
-  s.Cb = s.Ct * s.Cz * s.Cy * s.Wm;
-  s.cell = s.Ct * s.Cz * s.Cy * s.Wc;
-  s.D1 = (int64_t)r[3] * s.Cz * s.Cy * s.Wc;
-  s.D2 = (int64_t)r[3] * r[2] * s.Cy * s.Wc;
-  s.D3 = (int64_t)r[3] * r[2] * r[1] * s.Wc;
-  s.words = (int64_t)r[3] * r[2] * r[1] * s.Wv;
-  s.nb = (s.words + kScanBlockWords - 1) / kScanBlockWords;
+  const int64_t Wm = (dims[0] + 63) / 64, Wv = ((int64_t)r[0] + 63) / 64;
+  s.a = dims[3] * dims[2] * Wm * r[1];
+  s.b = dims[3] * r[2] * Wm * r[1];
+  s.c = (int64_t)r[3] * r[2] * Wm * r[1];
+  s.rows = (int64_t)r[3] * r[2] * r[1];
+  s.bits = s.rows * Wv;
+  s.blk = (s.rows + kRows - 1) / kRows;
   s.Bx = ((int64_t)r[0] + 1) / 2;
   s.By = ((int64_t)r[1] + 1) / 2;
   s.Bz = ((int64_t)r[2] + 1) / 2;
@@ -297,98 +485,149 @@ int64_t index_dir_words(const fhash_grid_desc* g, int l) {
   return (int64_t)r[3] * r[2] * r[1] * (((int64_t)r[0] + 63) / 64);
 }
 
+namespace {
+
+// The workspace: the transposed mask, the arrays the passes alternate between
+// (y -> X, z -> Y, t -> X, x -> Y), row counts, block totals, level counts, and
+// the brick directory before its reordering.  Each is twice as large as the
+// level that needs most of it (kShare), so that the finest level goes alone
+// and the others in two or three groups: each group reads the mask once.
+constexpr int64_t kShare = 2;
+
+struct BuildWs {
+  int64_t mask, X, Y, rows, blk, bricks;  // words; rows in 4 bytes; bricks in 16
+  size_t bytes;
+};
+
+BuildWs build_ws(const fhash_grid_desc* g, const int64_t* dims) {
+  BuildWs w{};
+  w.mask = dims[3] * dims[2] * dims[1] * ((dims[0] + 63) / 64);
+  for (int l = 0; l < g->n_levels; ++l) {
+    const LevelSizes s = level_sizes(g->res[l], dims);
+    w.X = std::max(w.X, std::max(s.a, s.c));
+    w.Y = std::max(w.Y, std::max(s.b, s.bits));
+    w.rows = std::max(w.rows, s.rows);
+    w.blk = std::max(w.blk, s.blk);
+    if (g->layout == FHASH_LAYOUT_BRICKS) {
+      w.bricks = std::max(w.bricks, s.bwords);
+      w.blk = std::max(w.blk, s.bnb);
+    }
+  }
+  if (g->layout != FHASH_LAYOUT_BRICKS && g->n_levels > 1) {
+    w.X *= kShare;
+    w.Y *= kShare;
+    w.rows *= kShare;
+    w.blk *= kShare;
+  }
+  w.bytes = align256(w.mask * 8) + align256(w.X * 8) + align256(w.Y * 8) + align256(w.rows * 4) +
+            align256(w.blk * 8) + align256(8 * FHASH_MAX_LEVELS) + align256(w.bricks * 16);
+  return w;
+}
+
+}  // namespace
+
 size_t index_workspace_bytes(const fhash_grid_desc* g, const int64_t* dims) {
-  int64_t b0 = 1, b1 = 1, nb = 1;
-  for (int l = 0; l < g->n_levels; ++l) {
-    LevelSizes s = level_sizes(g->res[l], dims);
-    b0 = std::max(b0, std::max(std::max(s.A, s.Cb), std::max(s.D1, s.D3)));
-    b1 = std::max(b1, std::max(std::max(s.B, s.cell), s.D2));
-    nb = std::max(nb, s.nb);
-  }
-  int64_t words = 1, bwords = 1;
-  for (int l = 0; l < g->n_levels; ++l) {
-    LevelSizes ls = level_sizes(g->res[l], dims);
-    words = std::max(words, ls.words);
-    bwords = std::max(bwords, ls.bwords);
-    nb = std::max(nb, ls.bnb);
-  }
-  const bool bricks = g->layout == FHASH_LAYOUT_BRICKS;
-  return align256(b0 * 8) + align256(b1 * 8) + align256(nb * 8) + align256(8 * FHASH_MAX_LEVELS) +
-         align256(words * 16) + (bricks ? align256(bwords * 16) : 0);
+  return build_ws(g, dims).bytes;
 }
 
 hipError_t launch_build_index(const fhash_grid_desc* g, const uint64_t* mask,
                               const int64_t* dims, ulonglong2* dir, const int64_t* dir_off,
                               void* ws, uint64_t* counts_host, hipStream_t st) {
   const bool bricks = g->layout == FHASH_LAYOUT_BRICKS;
-  int64_t b0 = 1, b1 = 1, nbmax = 1, wmax = 1;
-  for (int l = 0; l < g->n_levels; ++l) {
-    LevelSizes s = level_sizes(g->res[l], dims);
-    b0 = std::max(b0, std::max(std::max(s.A, s.Cb), std::max(s.D1, s.D3)));
-    b1 = std::max(b1, std::max(std::max(s.B, s.cell), s.D2));
-    nbmax = std::max(nbmax, std::max(s.nb, s.bnb));
-    wmax = std::max(wmax, s.words);
-  }
+  const BuildWs w = build_ws(g, dims);
   char* p = static_cast<char*>(ws);
-  uint64_t* buf0 = reinterpret_cast<uint64_t*>(p);
-  p += align256(b0 * 8);
-  uint64_t* buf1 = reinterpret_cast<uint64_t*>(p);
-  p += align256(b1 * 8);
-  uint64_t* partial = reinterpret_cast<uint64_t*>(p);
-  p += align256(nbmax * 8);
-  uint64_t* counts = reinterpret_cast<uint64_t*>(p);
-  p += align256(8 * FHASH_MAX_LEVELS);
-  ulonglong2* rowmajor = reinterpret_cast<ulonglong2*>(p);  // one level's directory, F-Hash order
-  p += align256(wmax * 16);
-  ulonglong2* bricked = reinterpret_cast<ulonglong2*>(p);   // brick-linear order (bricks only)
+  auto take = [&p](size_t bytes) {
+    char* q = p;
+    p += align256(bytes);
+    return q;
+  };
+  uint64_t* tmask = reinterpret_cast<uint64_t*>(take(w.mask * 8));
+  uint64_t* X = reinterpret_cast<uint64_t*>(take(w.X * 8));
+  uint64_t* Y = reinterpret_cast<uint64_t*>(take(w.Y * 8));
+  uint32_t* row_count = reinterpret_cast<uint32_t*>(take(w.rows * 4));
+  uint64_t* partial = reinterpret_cast<uint64_t*>(take(w.blk * 8));
+  uint64_t* counts = reinterpret_cast<uint64_t*>(take(8 * FHASH_MAX_LEVELS));
+  ulonglong2* bricked = reinterpret_cast<ulonglong2*>(take(w.bricks * 16));
 
   const int T = 256;
-  const int64_t Sx = dims[0], Sy = dims[1], Sz = dims[2], St = dims[3];
-  for (int l = 0; l < g->n_levels; ++l) {
-    const int32_t* r = g->res[l];
-    LevelSizes s = level_sizes(r, dims);
-    // Active cells: reduce t, z, y over whole words, then x over bit ranges.
-    hipLaunchKernelGGL(or_reduce_axis_kernel, dim3(grid_for(s.A, T)), dim3(T), 0, st, mask, buf0,
-                       (int64_t)1, St, s.Ct, Sz * Sy * s.Wm, (int64_t)r[3]);
-    hipLaunchKernelGGL(or_reduce_axis_kernel, dim3(grid_for(s.B, T)), dim3(T), 0, st, buf0, buf1,
-                       s.Ct, Sz, s.Cz, Sy * s.Wm, (int64_t)r[2]);
-    hipLaunchKernelGGL(or_reduce_axis_kernel, dim3(grid_for(s.Cb, T)), dim3(T), 0, st, buf1, buf0,
-                       s.Ct * s.Cz, Sy, s.Cy, s.Wm, (int64_t)r[1]);
-    hipLaunchKernelGGL(cells_x_kernel, dim3(grid_for(s.cell, T)), dim3(T), 0, st, buf0, buf1,
-                       s.Ct * s.Cz * s.Cy, s.Wm, s.Wc, Sx, (int64_t)r[0]);
-    // Active vertices: corners of active cells (dilate by one step per axis).
-    hipLaunchKernelGGL(dilate_axis_kernel, dim3(grid_for(s.D1, T)), dim3(T), 0, st, buf1, buf0,
-                       (int64_t)1, s.Ct, s.Cz * s.Cy * s.Wc);
-    hipLaunchKernelGGL(dilate_axis_kernel, dim3(grid_for(s.D2, T)), dim3(T), 0, st, buf0, buf1,
-                       (int64_t)r[3], s.Cz, s.Cy * s.Wc);
-    hipLaunchKernelGGL(dilate_axis_kernel, dim3(grid_for(s.D3, T)), dim3(T), 0, st, buf1, buf0,
-                       (int64_t)r[3] * r[2], s.Cy, s.Wc);
-    ulonglong2* d = rowmajor;
-    hipLaunchKernelGGL(vert_x_kernel, dim3(grid_for(s.words, T)), dim3(T), 0, st, buf0, d,
-                       (int64_t)r[3] * r[2] * r[1], s.Wc, s.Wv);
-    // Order of the ranks: F-Hash rows, or bricks (then the words are regrouped first).
-    int64_t words = s.words, nb = s.nb, nrows = (int64_t)r[3] * r[2] * r[1], ry = r[1],
-            wv = s.Wv;
-    if (bricks) {
-      hipLaunchKernelGGL(brickify_kernel, dim3(grid_for(s.bwords, T)), dim3(T), 0, st, rowmajor,
-                         bricked, (int64_t)r[0], (int64_t)r[1], (int64_t)r[2], (int64_t)r[3],
-                         s.Wv, s.Wb, s.By, s.Bz, s.bwords);
-      d = bricked;
-      words = s.bwords;
-      nb = s.bnb;
-      nrows = s.Bt * s.Bz * s.By;
-      ry = s.By;
-      wv = s.Wb;
+  GroupBuild G{};
+  G.Sx = dims[0];
+  G.Sy = dims[1];
+  G.Sz = dims[2];
+  G.St = dims[3];
+  G.Wm = (dims[0] + 63) / 64;
+  const int64_t tiles = G.St * G.Sz * ((G.Sy + 63) / 64) * ((G.Wm + kTileW - 1) / kTileW);
+  hipLaunchKernelGGL(transpose_kernel, dim3(grid_for(tiles, 1)), dim3(T), 0, st, mask, tmask,
+                     G.St * G.Sz, G.Sy, G.Wm);
+  int l0 = 0;
+  while (l0 < g->n_levels) {
+    // the next levels that fit the workspace together, coarsest first (a brick
+    // level has the brick arrays to itself)
+    int64_t a = 0, b = 0, c = 0, bits = 0, rows = 0, blk = 0, maxrows = 0, maxb = 0, maxc = 0;
+    int n = 0;
+    while (l0 + n < g->n_levels) {
+      const int32_t* r = g->res[l0 + n];
+      const LevelSizes s = level_sizes(r, dims);
+      if (n > 0 && (bricks || std::max(a + s.a, c + s.c) > w.X ||
+                    std::max(b + s.b, bits + s.bits) > w.Y || rows + s.rows > w.rows ||
+                    blk + s.blk > w.blk))
+        break;
+      LevelBuild& d = G.lv[n];
+      d.rx = r[0];
+      d.ry = r[1];
+      d.rz = r[2];
+      d.rt = r[3];
+      d.wv = (r[0] + 63) / 64;
+      d.y0 = n == 0 ? 0 : G.lv[n - 1].y0 + G.lv[n - 1].ry;
+      d.a = a;
+      d.b = b;
+      d.c = c;
+      d.bits = bits;
+      d.row = rows;
+      d.blk = blk;
+      d.dir = dir_off[l0 + n];
+      a += s.a;
+      b += s.b;
+      c += s.c;
+      bits += s.bits;
+      rows += s.rows;
+      blk += s.blk;
+      maxrows = std::max(maxrows, s.blk);
+      maxb = std::max(maxb, s.b / r[2]);
+      maxc = std::max(maxc, s.c / r[3]);
+      ++n;
     }
-    // Ranks: exclusive prefix sum of popcounts.
-    hipLaunchKernelGGL(popc_block_sums_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st,
-                       d, words, partial);
-    hipLaunchKernelGGL(scan_partials_kernel, dim3(1), dim3(1024), 0, st, partial, nb,
-                       counts + l);
-    hipLaunchKernelGGL(write_ranks_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, d,
-                       words, partial);
-    hipLaunchKernelGGL(dir_interleave_kernel, dim3(grid_for(words, T)), dim3(T), 0, st, d,
-                       dir + dir_off[l], nrows, ry, wv);
+    // or_axis: a thread per line, or kLineThreads where the lines are fewer
+    hipLaunchKernelGGL(or_y_kernel, dim3(grid_for(G.St * G.Sz * G.Wm, 1)), dim3(T), 0, st, G,
+                       G.lv[n - 1].y0 + G.lv[n - 1].ry, tmask, X);
+    hipLaunchKernelGGL(or_z_kernel, dim3(grid_for(std::max(maxb, kLineThreads), T), n),
+                       dim3(T), 0, st, G, X, Y);
+    hipLaunchKernelGGL(or_t_kernel, dim3(grid_for(std::max(maxc, kLineThreads), T), n),
+                       dim3(T), 0, st, G, Y, X);
+    hipLaunchKernelGGL(rows_kernel, dim3((unsigned)maxrows, n), dim3(256), 0, st, G, X, Y,
+                       row_count, partial);
+    if (!bricks) {
+      hipLaunchKernelGGL(scan_rows_kernel, dim3(n), dim3(1024), 0, st, G, partial, counts + l0);
+      hipLaunchKernelGGL(entries_kernel,
+                         dim3((unsigned)((maxrows + kScanThreads / kRows - 1) /
+                                         (kScanThreads / kRows)), n),
+                         dim3(kScanThreads), 0, st, G, Y, row_count, partial, dir);
+    } else {
+      const int32_t* r = g->res[l0];
+      const LevelSizes s = level_sizes(r, dims);
+      hipLaunchKernelGGL(brickify_kernel, dim3(grid_for(s.bwords, T)), dim3(T), 0, st, Y, bricked,
+                         (int64_t)r[0], (int64_t)r[1], (int64_t)r[2], (int64_t)r[3],
+                         (int64_t)G.lv[0].wv, s.Wb, s.By, s.Bz, s.bwords);
+      hipLaunchKernelGGL(popc_block_sums_kernel, dim3((unsigned)s.bnb), dim3(kScanThreads), 0, st,
+                         bricked, s.bwords, partial);
+      hipLaunchKernelGGL(scan_partials_kernel, dim3(1), dim3(1024), 0, st, partial, s.bnb,
+                         counts + l0);
+      hipLaunchKernelGGL(write_ranks_kernel, dim3((unsigned)s.bnb), dim3(kScanThreads), 0, st,
+                         bricked, s.bwords, partial);
+      hipLaunchKernelGGL(dir_interleave_kernel, dim3(grid_for(s.bwords, T)), dim3(T), 0, st,
+                         bricked, dir + dir_off[l0], s.Bt * s.Bz * s.By, s.By, s.Wb);
+    }
+    l0 += n;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
