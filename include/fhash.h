@@ -271,12 +271,10 @@ int fhash_fused_fwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
                     const void* table, fhash_dtype table_dt, const float* params,
                     const void* shadow, float* y, void* stream);
 /* flags: FHASH_SAMPLES_SORTED declares that the batch is ordered by
- * fhash_sort_samples; on the levels coarse enough for neighbouring samples to
- * share vertices, the scatter-add then sums a corner across the samples that
- * one of its instructions covers (16 at F = 1 and 2, 8 at F = 4) when they all
- * hit the same slot, and adds the sum with one atomic (atomics of different
- * lanes into one float cannot share a memory request).  Results are the same
- * up to FP32 summation order.  FHASH_GRAD_PAIRED: d_table is stored in runs
+ * fhash_sort_samples: the coarse levels are then summed as under
+ * FHASH_COARSE_LDS below (not by fhash_fused_train_static, which has no
+ * workspace for it).  Results are the same up to FP32 summation order.
+ * FHASH_GRAD_PAIRED: d_table is stored in runs
  * of 16 floats separated by 16-float gaps (gradient value i at
  * d_table[i + 16 floor(i / 16)]; the gradient array of the optimiser layout
  * FHASH_MOMENTS_WITH_PARAMS below); the table read is independent of it

@@ -163,6 +163,32 @@ static int apply_touch(const fhash_touch* t, int64_t len, fh::GridDev* g) {
   return FHASH_OK;
 }
 
+// Levels 0 .. lc - 1 whose gradient goes through the LDS scatter (row order
+// only).  FHASH_COARSE_LDS and FHASH_SAMPLES_SORTED: the coarse levels with at
+// most one cell per sample of the batch, where the chunks of a sorted batch
+// share vertices.  In any batch: levels so small that their whole vertex box
+// fits the LDS image and that every vertex takes 16 or more corners' adds
+// (n >= vertices): atomics into one 64-byte line are performed one after
+// another, about 10 ns each, so levels of a few vertices held the backward of
+// 65,537 points on a fold-2 dense box (F = 1, levels of 16 to 2,760 vertices and
+// larger) for 7.8 ms; through LDS the same backward takes 0.18 + 0.05 ms.  At
+// the edge (4,096 samples, 1,536 vertices, F = 2) the step takes 77 us with the
+// level in LDS, 102 us with it and a level of 128 vertices in the kernel.
+static int coarse_levels(const fhash_index* idx, int64_t n, uint32_t flags) {
+  if (idx->grid.layout != FHASH_LAYOUT_ROWS) return 0;
+  const bool shared = (flags & (FHASH_COARSE_LDS | FHASH_SAMPLES_SORTED)) != 0;
+  int lc = 0;
+  for (int l = 0; l < idx->grid.n_levels; ++l) {
+    const int32_t* r = idx->grid.res[l];
+    const double cells = (double)(r[0] - 1) * (r[1] - 1) * (r[2] - 1) * (r[3] - 1);
+    const double verts = (double)r[0] * r[1] * r[2] * r[3];
+    const bool small = verts * idx->grid.n_features <= fh::kCoarseFloats && verts <= (double)n;
+    if (!small && !(shared && cells <= (double)n)) break;
+    lc = l + 1;
+  }
+  return lc;
+}
+
 extern "C" {
 
 int fhash_version(void) { return FHASH_VERSION; }
@@ -317,6 +343,7 @@ int fhash_encode_bwd(const fhash_index* idx, const float* pos, int64_t n, const 
   if (pos == nullptr || d_enc == nullptr || d_table == nullptr)
     return fail(FHASH_EINVAL, "NULL pointer");
   if (!aligned16(pos)) return fail(FHASH_EINVAL, "pos not 16-byte aligned");
+  g.coarse = coarse_levels(idx, n, 0);
   return hip_status(fh::launch_encode_bwd(g, pos, n, d_enc, d_table, S(stream)),
                     "fhash_encode_bwd");
 }
@@ -357,33 +384,6 @@ int fhash_mlp_bwd(const fhash_mlp_desc* mlp, const float* params, const void* sh
   return hip_status(
       fh::launch_mlp_bwd(mlp->width[0], H, NH, params, x, dy, n, d_params, dx, ws, P, S(stream)),
       "fhash_mlp_bwd");
-}
-
-// Levels whose cell count is at most 8 samples' worth: sorted neighbours share
-// their vertices often enough for the merge of a scatter pass to pay.
-static uint32_t dedup_mask(const fhash_index* idx, int64_t n, uint32_t flags) {
-  if (!(flags & FHASH_SAMPLES_SORTED)) return 0u;
-  uint32_t m = 0;
-  for (int l = 0; l < idx->grid.n_levels; ++l) {
-    const int32_t* r = idx->grid.res[l];
-    const double cells = (double)(r[0] - 1) * (r[1] - 1) * (r[2] - 1) * (r[3] - 1);
-    if (cells <= 8.0 * (double)n) m |= 1u << l;
-  }
-  return m;
-}
-
-// FHASH_COARSE_LDS: levels 0 .. lc - 1, the coarse levels with at most one
-// cell per sample of the batch, go through the LDS scatter (row order only).
-static int coarse_levels(const fhash_index* idx, int64_t n, uint32_t flags) {
-  if (!(flags & FHASH_COARSE_LDS) || idx->grid.layout != FHASH_LAYOUT_ROWS) return 0;
-  int lc = 0;
-  for (int l = 0; l < idx->grid.n_levels; ++l) {
-    const int32_t* r = idx->grid.res[l];
-    const double cells = (double)(r[0] - 1) * (r[1] - 1) * (r[2] - 1) * (r[3] - 1);
-    if (cells > (double)n) break;
-    lc = l + 1;
-  }
-  return lc;
 }
 
 // Workspace of a fused backward: the decoder-gradient partials, then the
@@ -476,7 +476,6 @@ int fhash_fused_bwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
   fh::GridDev g;
   fh::make_grid_dev(idx, &g);
   if ((rc = apply_bwd_flags(flags, &g))) return rc;
-  g.dedup = dedup_mask(idx, n, flags);
   set_coarse(&g, lc, n, P, ws);
   if ((rc = apply_touch(touch, total_rows(idx) * idx->grid.n_features, &g))) return rc;
   const fhash_dtype tdt = table_view(table_dt, &g);
@@ -506,7 +505,6 @@ int fhash_fused_train(const fhash_index* idx, const fhash_mlp_desc* mlp, const f
   fh::GridDev g;
   fh::make_grid_dev(idx, &g);
   if ((rc = apply_bwd_flags(flags, &g))) return rc;
-  g.dedup = dedup_mask(idx, n, flags);
   set_coarse(&g, lc, n, P, ws);
   if ((rc = apply_touch(touch, total_rows(idx) * idx->grid.n_features, &g))) return rc;
   const fhash_dtype tdt = table_view(table_dt, &g);
@@ -542,7 +540,6 @@ int fhash_fused_train_static(const fhash_index* idx, const fhash_mlp_desc* mlp,
   fh::GridDev g;
   fh::make_grid_dev(idx, &g);
   if ((rc = apply_bwd_flags(flags, &g))) return rc;
-  g.dedup = dedup_mask(idx, n, flags);
   if ((rc = apply_touch(touch, total_rows(idx) * idx->grid.n_features, &g))) return rc;
   const fhash_dtype tdt = table_view(table_dt, &g);
   return hip_status(fh::launch_fused_train(g, H, NH, mlp->compute_dt, pos, target, n, table,

@@ -1,7 +1,7 @@
-// Scatter-add of the coarsest levels' encoding gradient through LDS
-// (FHASH_COARSE_LDS).  The fused backward leaves the gradient of the encoding
-// of levels 0 .. g.coarse - 1 in dxc ([level][sample][feature]) instead of
-// adding it into the table; this kernel adds it.  Each workgroup takes one
+// Scatter-add of the coarsest levels' encoding gradient through LDS.  The
+// backward calls leave the gradient of levels 0 .. g.coarse - 1 (value k of
+// sample s and level l at grad[l * level_step + s * sample_step + k]) to this
+// kernel instead of adding it into the table.  Each workgroup takes one
 // level and a contiguous chunk of the batch (neighbours in space when the batch is
 // sorted), finds the box of the level's vertices its samples touch, sums the
 // 16 corner contributions of every sample into an LDS image of that box, and
@@ -24,10 +24,11 @@ namespace fh {
 namespace {
 
 constexpr int kThreads = 1024;  // 16 waves: the loops below wait on L2 latency
-constexpr int kChunk = 2048;    // samples per workgroup
+constexpr int kChunk = 2048;    // samples per workgroup, at most
+constexpr int kChunkMin = 256;  // and at least: a box is cleared and added per chunk
 constexpr int kUnroll = 4;      // independent loads in flight per thread
 constexpr int kParts = 4;       // a chunk whose box does not fit is retried in 4 parts
-constexpr int kCap = 16000;   // floats of the LDS image (with the reduction slots, under 64 KiB)
+constexpr int kCap = kCoarseFloats;  // floats of the LDS image (with the reduction slots, under 64 KiB)
 
 // Slot of vertex (x, y, z, t) of a rows-ordered level: dense, hashed, or
 // through the rank directory (valid = false for an inactive vertex).  Reads
@@ -54,17 +55,18 @@ __device__ __forceinline__ int64_t vertex_slot(const LevelDev& d, const ulonglon
 template <int F>
 __global__ void __launch_bounds__(kThreads)
     coarse_scatter_kernel(GridDev g, const float4* __restrict__ pos, int64_t n,
-                          const float* __restrict__ dxc, float* __restrict__ d_table) {
+                          const float* __restrict__ grad, int64_t level_step,
+                          int64_t sample_step, int chunk, float* __restrict__ d_table) {
   extern __shared__ float acc[];  // kCap floats
   __shared__ int red[8][kThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int64_t c0 = (int64_t)blockIdx.x * kChunk;
-  const int cnt = (int)((n - c0) < kChunk ? (n - c0) : kChunk);
+  const int64_t c0 = (int64_t)blockIdx.x * chunk;
+  const int cnt = (int)((n - c0) < chunk ? (n - c0) : chunk);
   const bool active = g.active != 0;
   {
     const int l = blockIdx.y;  // one level per workgroup row of the grid
     const LevelDev& d = g.lv[l];
-    const float* gl = dxc + (int64_t)l * n * F;
+    const float* gl = grad + l * level_step;
     int nparts = 1;
     for (int part = 0; part < nparts; ++part) {
     // samples s0 .. s0 + bn - 1: the chunk, or one of its parts
@@ -138,7 +140,7 @@ __global__ void __launch_bounds__(kThreads)
           const int i = i0 + u;
           pu[u] = i < ie ? pos[s0 + i] : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-          for (int k = 0; k < F; ++k) gu[u][k] = i < ie ? gl[(s0 + i) * F + k] : 0.0f;
+          for (int k = 0; k < F; ++k) gu[u][k] = i < ie ? gl[(s0 + i) * sample_step + k] : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
@@ -230,7 +232,7 @@ __global__ void __launch_bounds__(kThreads)
         bool valid;
         const int64_t sl = vertex_slot(d, g.dir, active, ct + ot, cz + oz, cy + oy, cx + ox, valid);
         if (valid) {
-          unsafeAtomicAdd(d_table + run_off(sl * F, g.gmask) + k, w * gl[(s0 + i) * F + k]);
+          unsafeAtomicAdd(d_table + run_off(sl * F, g.gmask) + k, w * gl[(s0 + i) * sample_step + k]);
           if (k == 0) mark_touched(g.touch, g.touch_begin, sl * F);
         }
       }
@@ -240,25 +242,30 @@ __global__ void __launch_bounds__(kThreads)
 }
 
 template <int F>
-hipError_t launch_f(const GridDev& g, const float* pos, int64_t n, float* d_table,
-                    hipStream_t st) {
-  const int64_t blocks = (n + kChunk - 1) / kChunk;
+hipError_t launch_f(const GridDev& g, const float* pos, int64_t n, const float* grad,
+                    int64_t level_step, int64_t sample_step, float* d_table, hipStream_t st) {
+  // about two workgroups per CU: a short batch in shorter chunks
+  int chunk = kChunk;
+  while (chunk > kChunkMin && (n + chunk - 1) / chunk * g.coarse < 512) chunk /= 2;
+  const int64_t blocks = (n + chunk - 1) / chunk;
   hipLaunchKernelGGL(coarse_scatter_kernel<F>, dim3((unsigned)blocks, (unsigned)g.coarse),
-                     dim3(kThreads),
-                     kCap * sizeof(float), st, g, reinterpret_cast<const float4*>(pos), n,
-                     g.dxc, d_table);
+                     dim3(kThreads), kCap * sizeof(float), st, g,
+                     reinterpret_cast<const float4*>(pos), n, grad, level_step, sample_step, chunk,
+                     d_table);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_coarse_scatter(const GridDev& g, const float* pos, int64_t n, float* d_table,
+hipError_t launch_coarse_scatter(const GridDev& g, const float* pos, int64_t n, const float* grad,
+                                 int64_t level_step, int64_t sample_step, float* d_table,
                                  hipStream_t st) {
   if (g.coarse <= 0 || n == 0) return hipSuccess;
   switch (g.F) {
-    case 1: return launch_f<1>(g, pos, n, d_table, st);
-    case 2: return launch_f<2>(g, pos, n, d_table, st);
-    case 4: return launch_f<4>(g, pos, n, d_table, st);
+    case 1: return launch_f<1>(g, pos, n, grad, level_step, sample_step, d_table, st);
+    case 2: return launch_f<2>(g, pos, n, grad, level_step, sample_step, d_table, st);
+    case 4: return launch_f<4>(g, pos, n, grad, level_step, sample_step, d_table, st);
+    case 8: return launch_f<8>(g, pos, n, grad, level_step, sample_step, d_table, st);
   }
   return hipErrorInvalidValue;
 }

@@ -26,7 +26,6 @@ struct GridDev {
   const ulonglong2* dir;  // {bits, rank-before-word}; NULL when dense
   int32_t L, F;
   int32_t active;
-  uint32_t dedup;  // bit l: combine equal slots of neighbouring lanes before level l's atomics
   uint8_t* touch;  // touched-segment flags of the table gradient (NULL: not tracked)
   int64_t touch_begin;  // first tracked float (a multiple of FHASH_TOUCH_FLOATS)
   // run masks of the table read and of the table gradient (run_off): 0, dense;
@@ -54,7 +53,6 @@ inline void make_grid_dev(const fhash_index* idx, GridDev* g) {
   g->F = gd.n_features;
   g->active = idx->active;
   g->dir = reinterpret_cast<const ulonglong2*>(idx->dir);
-  g->dedup = 0;
   g->touch = nullptr;
   g->touch_begin = 0;
   g->tmask = 0;

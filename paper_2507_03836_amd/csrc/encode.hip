@@ -37,25 +37,42 @@ __global__ void __launch_bounds__(256)
   for (int k = 0; k < F; ++k) o[k] = out[0][k];
 }
 
-// 2F threads per sample (pair element x feature), see scatter_level_lane.
-template <int F>
+// Rows order: one thread per sample and level, levels fastest, in groups of 2F
+// that add their members' samples one after another (scatter_rows); levels
+// below g.coarse are left to the LDS scatter.  Brick order: 2F threads per
+// sample (pair element x feature), a loop over the levels.
+template <int F, bool BRICK>
 __global__ void __launch_bounds__(256)
     encode_bwd_kernel(GridDev g, const float4* __restrict__ pos, int64_t n,
                       const float* __restrict__ d_enc, float* __restrict__ d_table) {
-  constexpr int Q = 2 * F;
+  __shared__ LevelDev lv[FHASH_MAX_LEVELS];
+  if (threadIdx.x < FHASH_MAX_LEVELS) lv[threadIdx.x] = g.lv[threadIdx.x];
+  __syncthreads();
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t s = t / Q;
-  if (s >= n) return;
-  const int r = (int)(t % Q), e = r / F, f = r % F;
-  const float4 p = pos[s];
-  const float* gin = d_enc + s * (int64_t)g.L * F;
-  for (int l = 0; l < g.L; ++l) {
-    if (g.lv[l].brick)
-      scatter_level_lane<F, true>(g.lv[l], g.dir, g.active != 0, p, e, f, gin[l * F + f],
-                                  d_table, g.touch, g.touch_begin, g.gmask);
-    else
-      scatter_level_lane<F, false>(g.lv[l], g.dir, g.active != 0, p, e, f, gin[l * F + f],
-                                   d_table, g.touch, g.touch_begin, g.gmask);
+  if constexpr (BRICK) {
+    constexpr int Q = 2 * F;
+    const int64_t s = t / Q;
+    if (s >= n) return;
+    const int r = (int)(t % Q), e = r / F, f = r % F;
+    const float4 p = pos[s];
+    const float* gin = d_enc + s * (int64_t)g.L * F;
+    for (int l = 0; l < g.L; ++l)
+      scatter_brick_lane<F>(lv[l], g.dir, g.active != 0, p, e, f, gin[l * F + f], d_table,
+                            g.touch, g.touch_begin, g.gmask);
+  } else {
+    const int64_t s = t / g.L;
+    const int l = (int)(t - s * g.L);
+    const bool own = s < n && l >= g.coarse;
+    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+    float gr[F];
+#pragma unroll
+    for (int k = 0; k < F; ++k) gr[k] = 0.0f;
+    if (own) {
+      p = pos[s];
+#pragma unroll
+      for (int k = 0; k < F; ++k) gr[k] = d_enc[t * F + k];
+    }
+    scatter_rows<F>(g, lv[l], p, own, gr, d_table);
   }
 }
 
@@ -139,11 +156,16 @@ hipError_t launch_fwd_t(const GridDev& g, const float* pos, int64_t n, const voi
 template <int F>
 hipError_t launch_bwd_t(const GridDev& g, const float* pos, int64_t n, const float* d_enc,
                         float* d_table, hipStream_t st) {
-  const int T = 256;
-  const int64_t blocks = (n * 2 * F + T - 1) / T;
-  hipLaunchKernelGGL((encode_bwd_kernel<F>), dim3((unsigned)blocks), dim3(T), 0, st, g,
-                     reinterpret_cast<const float4*>(pos), n, d_enc, d_table);
-  return hipGetLastError();
+  const float4* p = reinterpret_cast<const float4*>(pos);
+  if (g.lv[0].brick)
+    hipLaunchKernelGGL((encode_bwd_kernel<F, true>), dim3((unsigned)((n * 2 * F + 255) / 256)),
+                       dim3(256), 0, st, g, p, n, d_enc, d_table);
+  else
+    hipLaunchKernelGGL((encode_bwd_kernel<F, false>), dim3((unsigned)((n * g.L + 255) / 256)),
+                       dim3(256), 0, st, g, p, n, d_enc, d_table);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || g.coarse == 0) return e;
+  return launch_coarse_scatter(g, pos, n, d_enc, F, (int64_t)g.L * F, d_table, st);
 }
 
 }  // namespace

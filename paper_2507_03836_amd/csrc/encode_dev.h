@@ -3,6 +3,8 @@
 #pragma once
 #include <hip/hip_fp16.h>
 
+#include <utility>
+
 #include "common.h"
 
 namespace fh {
@@ -243,71 +245,30 @@ __device__ __forceinline__ void mark_touched(uint8_t* touch, int64_t tbeg, int64
   if (touch != nullptr && fidx >= tbeg) touch[fidx / FHASH_TOUCH_FLOATS] = 1;
 }
 
-// Adjoint of encode_level: d_table[slot_c][k] += w_c g[k] with FP32 hardware
-// atomics (no return value).  Weights are recomputed from the position.
-// gmask: the gradient's run mask (run_off); touch flags index the logical
-// floats.
-template <int F, bool BRICK = false>
-__device__ __forceinline__ void scatter_level(const LevelDev& d, const ulonglong2* dir,
-                                              bool active, const float4 p, const float* g,
-                                              float* __restrict__ d_table, uint8_t* touch,
-                                              int64_t tbeg, int64_t gmask) {
-  int ix, iy, iz, it;
-  float fx, fy, fz, ft;
-  locate(p.x, d.rx, d.sx, ix, fx);
-  locate(p.y, d.ry, d.sy, iy, fy);
-  locate(p.z, d.rz, d.sz, iz, fz);
-  locate(p.w, d.rt, d.st, it, ft);
-  const int a = pair_axis<BRICK>(ix, iy, iz, it);
-  const float fa = pair_frac(a, fx, fy, fz, ft);
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    float wr;
-    int64_t s0, s1;
-    bool v0, v1;
-    corner_pair<BRICK>(d, dir, active, ix, iy, iz, it, fx, fy, fz, ft, a, r, s0, s1, v0, v1, wr);
-    const float w0 = wr * (1.0f - fa), w1 = wr * fa;
-    if (v0) {
-#pragma unroll
-      for (int k = 0; k < F; ++k) unsafeAtomicAdd(d_table + run_off(s0 * F, gmask) + k, w0 * g[k]);
-      mark_touched(touch, tbeg, s0 * F);
-    }
-    if (v1) {
-#pragma unroll
-      for (int k = 0; k < F; ++k) unsafeAtomicAdd(d_table + run_off(s1 * F, gmask) + k, w1 * g[k]);
-      mark_touched(touch, tbeg, s1 * F);
-    }
-  }
-}
-
-// One lane's share of a level's scatter-add.  The lane owns pair element e
-// (the first or second corner of every corner pair, corner_pair) and feature f
-// of one sample: 2F consecutive lanes own one sample, so the 2F atomics they
-// issue together hit the two slots of one pair (8F contiguous bytes in the
-// rows layout and for x pairs inside a brick; 4F-byte halves a few rows apart
-// inside one brick otherwise).  Atomics of one
-// instruction that fall in the same 64-byte segment are performed as one
-// memory transaction, which is what bounds the scatter on gfx950.
-template <int F, bool BRICK = false>
-__device__ __forceinline__ void scatter_level_lane(const LevelDev& d, const ulonglong2* dir,
+// One lane's share of a level's scatter-add, brick order.  The lane owns pair
+// element e (the first or second corner of every corner pair, corner_pair) and
+// feature f of one sample: 2F consecutive lanes own one sample, so the 2F
+// atomics they issue together hit the two slots of one pair (8F contiguous
+// bytes for x pairs inside a brick; 4F-byte halves a few rows apart inside one
+// brick otherwise).  Atomics of one instruction that fall in the same 64-byte
+// segment are performed as one memory transaction, which is what bounds the
+// scatter on gfx950.
+template <int F>
+__device__ __forceinline__ void scatter_brick_lane(const LevelDev& d, const ulonglong2* dir,
                                                    bool active, const float4 p, int e, int f,
                                                    float gval, float* __restrict__ d_table,
                                                    uint8_t* touch, int64_t tbeg, int64_t gmask) {
-  int ix, iy, iz, it;
-  float fx, fy, fz, ft;
-  locate(p.x, d.rx, d.sx, ix, fx);
-  locate(p.y, d.ry, d.sy, iy, fy);
-  locate(p.z, d.rz, d.sz, iz, fz);
-  locate(p.w, d.rt, d.st, it, ft);
-  const int a = pair_axis<BRICK>(ix, iy, iz, it);
-  const float fa = pair_frac(a, fx, fy, fz, ft);
+  const Cell c = locate_cell(d, p);
+  const int a = pair_axis<true>(c.x, c.y, c.z, c.t);
+  const float fa = pair_frac(a, c.fx, c.fy, c.fz, c.ft);
   const float wx = e ? fa : 1.0f - fa;
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     float wr;
     int64_t s0, s1;
     bool v0, v1;
-    corner_pair<BRICK>(d, dir, active, ix, iy, iz, it, fx, fy, fz, ft, a, r, s0, s1, v0, v1, wr);
+    corner_pair<true>(d, dir, active, c.x, c.y, c.z, c.t, c.fx, c.fy, c.fz, c.ft, a, r, s0, s1,
+                      v0, v1, wr);
     const int64_t s = e ? s1 : s0;
     if (e ? v1 : v0) {
       unsafeAtomicAdd(d_table + run_off(s * F, gmask) + f, wr * wx * gval);
@@ -316,59 +277,118 @@ __device__ __forceinline__ void scatter_level_lane(const LevelDev& d, const ulon
   }
 }
 
-// scatter_level_lane for a batch in cell order (fhash_sort_samples): a pass
-// of the scatter holds one level for W / 2F samples (the W lanes that share
-// the level: 64, or 32 at F = 1), and at the coarse levels neighbouring
-// samples often all fall on the same vertex.  Lanes that add into the same
-// float of one chunk cannot share a memory request, so a corner that every
-// sample of the pass hits on one slot is summed across the samples first
-// (xor shuffles) and added by the first sample's lanes alone; any other corner
-// is added lane by lane.  Every lane of the W-lane group calls it (a sample
-// that is not valid passes valid = false and adds nothing).
-template <int F, bool BRICK = false>
-__device__ __forceinline__ void scatter_level_lane_merge(const LevelDev& d, const ulonglong2* dir,
-                                                         bool active, const float4 p, bool valid,
-                                                         int e, int f, float gval,
-                                                         float* __restrict__ d_table,
-                                                         uint8_t* touch, int64_t tbeg,
-                                                         int64_t gmask) {
+// The value lane K of the caller's group of Q lanes holds (K a constant): a
+// DPP move inside groups of 2 and 4, a swizzle inside groups of 8 and 16.
+template <int Q, int K>
+__device__ __forceinline__ int group_get(int x) {
+  static_assert(Q == 2 || Q == 4 || Q == 8 || Q == 16, "group size");
+  if constexpr (Q == 2)
+    return __builtin_amdgcn_update_dpp(0, x, K ? 0xF5 : 0xA0, 0xF, 0xF, false);
+  else if constexpr (Q == 4)
+    return __builtin_amdgcn_update_dpp(0, x, K * 0x55, 0xF, 0xF, false);
+  else
+    return __builtin_amdgcn_ds_swizzle(x, (32 - Q) | (K << 5));
+}
+template <int Q, int K>
+__device__ __forceinline__ float group_get(float x) {
+  return __int_as_float(group_get<Q, K>(__float_as_int(x)));
+}
+template <int Q, int K>
+__device__ __forceinline__ int64_t group_get(int64_t x) {
+  const uint32_t lo = (uint32_t)group_get<Q, K>((int)(uint32_t)x);
+  const uint32_t hi = (uint32_t)group_get<Q, K>((int)(x >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// What a lane brings to the scatter of its own sample and level, rows layout.
+template <int F>
+struct ScatterLane {
+  RowPairs p;  // p.v = 0: nothing to add
+  float wr[8], fx, g[F];
+  int64_t slot_off;
+};
+
+// Adjoint of encode_rows for one sample and level per lane: d_table[slot_c][k]
+// += w_c g[k] with FP32 hardware atomics.  Each lane has looked its own cell
+// up; pass K of 2F then has the 2F lanes of a group add the sample of the
+// group's lane K, lane (e, f) its pair element e and feature f, so the 2F
+// atomics of a pair fall in one or two 64-byte segments: atomics of one
+// instruction into one segment are performed as one memory transaction, which
+// is what bounds the scatter on gfx950.  Looking the cell up once and handing
+// the slots round takes the place of a lookup by every lane in every pass
+// (2F times the directory loads, each waited for): the fused training kernel of
+// 2^18 samples (16 levels, F = 2, FP32) took 1.87 ms so and takes 1.58, of 2^20
+// samples (FP16 decoder) 6.31 and 5.62, of 20,011 samples at F = 4 295 and 234
+// us.  Every lane of the wave calls it.
+template <int F, int K>
+__device__ __forceinline__ void scatter_pass(const GridDev& gd, const ScatterLane<F>& s, int e,
+                                             int f, float* __restrict__ d_table) {
   constexpr int Q = 2 * F;
-  constexpr int W = (16 * Q < 64) ? 16 * Q : 64;
-  const int lane = threadIdx.x & 63;
-  const int base = lane & ~(W - 1);
-  const int lead = base + (lane & (Q - 1));  // the same (e, f) lane of the first sample
-  const uint64_t group = (W == 64) ? ~0ull : (((1ull << W) - 1) << base);
-  int ix, iy, iz, it;
-  float fx, fy, fz, ft;
-  locate(p.x, d.rx, d.sx, ix, fx);
-  locate(p.y, d.ry, d.sy, iy, fy);
-  locate(p.z, d.rz, d.sz, iz, fz);
-  locate(p.w, d.rt, d.st, it, ft);
-  const int a = pair_axis<BRICK>(ix, iy, iz, it);
-  const float fa = pair_frac(a, fx, fy, fz, ft);
-  const float wx = e ? fa : 1.0f - fa;
+  const uint32_t v = (uint32_t)group_get<Q, K>((int)s.p.v);
+  const float fx = group_get<Q, K>(s.fx);
+  const float wx = e ? fx : 1.0f - fx;
+  float g = group_get<Q, K>(s.g[0]);
+#pragma unroll
+  for (int q = 1; q < F; ++q) {
+    const float t = group_get<Q, K>(s.g[q]);
+    if (f == q) g = t;
+  }
+  uint32_t hx = 0;
+  int64_t off = 0;
+  if (!gd.next_row) {  // hashed levels
+    hx = (uint32_t)group_get<Q, K>((int)s.p.hx);
+    off = group_get<Q, K>(s.slot_off);
+  }
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
-    float wr;
-    int64_t s0, s1;
-    bool v0, v1;
-    corner_pair<BRICK>(d, dir, active, ix, iy, iz, it, fx, fy, fz, ft, a, r, s0, s1, v0, v1, wr);
-    const int64_t s = (valid && (e ? v1 : v0)) ? (e ? s1 : s0) : -1;
-    float val = (s >= 0) ? wr * wx * gval : 0.0f;
-    const int64_t s_lead = __shfl(s, lead, 64);
-    const bool same = s_lead >= 0 && (s < 0 || s == s_lead);
-    if ((__ballot(same) & group) == group) {
-#pragma unroll
-      for (int o = Q; o < W; o <<= 1) val += __shfl_xor(val, o, 64);
-      if (lane == lead) {
-        unsafeAtomicAdd(d_table + run_off(s_lead * F, gmask) + f, val);
-        if (f == 0) mark_touched(touch, tbeg, s_lead * F);
-      }
-    } else if (s >= 0) {
-      unsafeAtomicAdd(d_table + run_off(s * F, gmask) + f, val);
-      if (f == 0) mark_touched(touch, tbeg, s * F);
+    const int64_t s0 = group_get<Q, K>(s.p.s[r]);
+    const float w = group_get<Q, K>(s.wr[r]);
+    if ((v >> (8 * e + r)) & 1u) {
+      const int64_t sl = e ? pair_second(s0, (v >> r) & 1u, hx, off) : s0;
+      unsafeAtomicAdd(d_table + run_off(sl * F, gd.gmask) + f, w * wx * g);
+      if (f == 0) mark_touched(gd.touch, gd.touch_begin, sl * F);  // one flag per slot
     }
   }
+}
+
+template <int F, int... K>
+__device__ __forceinline__ void scatter_passes(const GridDev& gd, const ScatterLane<F>& s, int e,
+                                               int f, float* __restrict__ d_table,
+                                               std::integer_sequence<int, K...>) {
+  (scatter_pass<F, K>(gd, s, e, f, d_table), ...);
+}
+
+// own: the lane has a sample and a level to add (with gradient g); the others
+// only help.
+template <int F>
+__device__ __forceinline__ void scatter_rows(const GridDev& gd, const LevelDev& d, const float4 p,
+                                             bool own, const float (&g)[F],
+                                             float* __restrict__ d_table) {
+  ScatterLane<F> s;
+  s.p.v = 0;
+  s.p.hx = 0;
+  s.fx = 0.0f;
+  s.slot_off = 0;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    s.p.s[r] = 0;
+    s.wr[r] = 0.0f;
+  }
+#pragma unroll
+  for (int k = 0; k < F; ++k) s.g[k] = g[k];
+  if (own) {
+    const Cell c = locate_cell(d, p);
+    RowEntries q;
+    row_fetch(d, gd.dir, gd.active != 0, c, q);
+    row_slots(d, gd.active != 0, c, q, s.p);
+    s.fx = c.fx;
+    s.slot_off = d.slot_off;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) s.wr[r] = row_weight(c, r);
+  }
+  const int lane = threadIdx.x & (2 * F - 1);
+  scatter_passes<F>(gd, s, lane / F, lane % F, d_table,
+                    std::make_integer_sequence<int, 2 * F>());
 }
 
 }  // namespace fh
