@@ -178,11 +178,11 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
   __shared__ __attribute__((aligned(16))) float lds[WFL + GFL + kWaves * WS + 1];
   __shared__ LevelDev lv[FHASH_MAX_LEVELS];
   if constexpr (MODE == MODE_FWD16)
-    load_weights_lds_h<INP, H, NH, D>(lds, A.params, A.in_w);
+    load_weights_lds_h<INP, H, NH, D, 64 * kWaves>(lds, A.params, A.in_w);
   else if constexpr (D32)
-    load_weights_lds<INP, H, NH>(lds, A.params, A.in_w);
+    load_weights_lds<INP, H, NH, 64 * kWaves>(lds, A.params, A.in_w);
   else
-    load_weights_lds_t<INP, H, NH, D>(lds, A.params, A.in_w);
+    load_weights_lds_t<INP, H, NH, D, 64 * kWaves>(lds, A.params, A.in_w);
   float* grad = lds + WFL;
   if constexpr (!FWD) grad_lds_zero<INP, H, NH>(grad);
   for (int e = threadIdx.x; e < FHASH_MAX_LEVELS; e += blockDim.x) lv[e] = g.lv[e];

@@ -9,17 +9,30 @@ namespace {
 
 constexpr int kWaves = 4;  // waves per workgroup
 
+// A lane's 4 consecutive inputs of each 16-feature block: one 16-byte load where
+// rows are a multiple of 4 floats on a 16-byte aligned array (vec).
 template <int INP>
 __device__ __forceinline__ void load_input_b(const float* __restrict__ x, int64_t smp, bool valid,
-                                             int in_w, float (&xb)[INP / 16][4]) {
+                                             int in_w, bool vec, float (&xb)[INP / 16][4]) {
   const int lane = threadIdx.x & 63, g = lane >> 4;
 #pragma unroll
-  for (int a = 0; a < INP / 16; ++a)
+  for (int a = 0; a < INP / 16; ++a) {
+    const int c0 = 16 * a + 4 * g;
+    if (vec) {
+      const float4 v = (valid && c0 < in_w)
+                           ? *reinterpret_cast<const float4*>(x + smp * in_w + c0)
+                           : make_float4(0.f, 0.f, 0.f, 0.f);
+      xb[a][0] = v.x, xb[a][1] = v.y, xb[a][2] = v.z, xb[a][3] = v.w;
+    } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c = 16 * a + 4 * g + i;
-      xb[a][i] = (valid && c < in_w) ? x[smp * in_w + c] : 0.0f;
+      for (int i = 0; i < 4; ++i)
+        xb[a][i] = (valid && c0 + i < in_w) ? x[smp * in_w + c0 + i] : 0.0f;
     }
+  }
+}
+
+__device__ __forceinline__ bool rows_of_float4(const float* x, int in_w) {
+  return in_w % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
 }
 
 template <int INP, int H, int NH>
@@ -28,16 +41,17 @@ __global__ void __launch_bounds__(64 * kWaves)
                    int in_w, float* __restrict__ y) {
   using S = MlpShape<INP, H, NH>;
   __shared__ __attribute__((aligned(16))) float lds[S::WFLOATS];
-  load_weights_lds<INP, H, NH>(lds, params, in_w);
+  load_weights_lds<INP, H, NH, 64 * kWaves>(lds, params, in_w);
   __syncthreads();
   const int lane = threadIdx.x & 63, g = lane >> 4, s = lane & 15;
+  const bool vec = rows_of_float4(x, in_w);
   const int64_t nblk = (n + 15) / 16;
   const int64_t nwav = (int64_t)gridDim.x * kWaves;
   for (int64_t b = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); b < nblk; b += nwav) {
     const int64_t smp = b * 16 + s;
     const bool valid = smp < n;
     float xb[S::INB][4];
-    load_input_b<INP>(x, smp, valid, in_w, xb);
+    load_input_b<INP>(x, smp, valid, in_w, vec, xb);
     float hs[NH][S::HB][4];
     const float yv = mlp_block_fwd<INP, H, NH>(lds, xb, hs);
     if (g == 0 && valid) y[smp] = yv;
@@ -52,7 +66,7 @@ __global__ void __launch_bounds__(64 * kWaves)
   using S = MlpShape<INP, H, NH>;
   constexpr int WS = mlp_wave_scratch<INP, H, NH>();
   __shared__ __attribute__((aligned(16))) float lds[S::WFLOATS + kWaves * WS];
-  load_weights_lds<INP, H, NH>(lds, params, in_w);
+  load_weights_lds<INP, H, NH, 64 * kWaves>(lds, params, in_w);
   __syncthreads();
   const int lane = threadIdx.x & 63, g = lane >> 4, s = lane & 15;
   const int wib = threadIdx.x >> 6;
@@ -60,13 +74,14 @@ __global__ void __launch_bounds__(64 * kWaves)
   const int64_t nblk = (n + 15) / 16;
   const int64_t nwav = (int64_t)gridDim.x * kWaves;
   const int64_t wave = (int64_t)blockIdx.x * kWaves + wib;
+  const bool vec = rows_of_float4(x, in_w), vecd = dx != nullptr && rows_of_float4(dx, in_w);
   MlpGrad<INP, H, NH> gr;
   gr.zero();
   for (int64_t b = wave; b < nblk; b += nwav) {
     const int64_t smp = b * 16 + s;
     const bool valid = smp < n;
     float xb[S::INB][4];
-    load_input_b<INP>(x, smp, valid, in_w, xb);
+    load_input_b<INP>(x, smp, valid, in_w, vec, xb);
     mlp_stage_input<INP, H, NH>(scratch, xb);
     float hs[NH][S::HB][4];
     mlp_block_fwd<INP, H, NH>(lds, xb, hs);
@@ -75,12 +90,18 @@ __global__ void __launch_bounds__(64 * kWaves)
     mlp_block_bwd<INP, H, NH>(lds, scratch, hs, dyv, gr, dxb);
     if (dx != nullptr && valid) {
 #pragma unroll
-      for (int a = 0; a < S::INB; ++a)
+      for (int a = 0; a < S::INB; ++a) {
+        const int c0 = 16 * a + 4 * g;
+        if (vecd) {
+          if (c0 < in_w)
+            *reinterpret_cast<float4*>(dx + smp * in_w + c0) =
+                make_float4(dxb[a][0], dxb[a][1], dxb[a][2], dxb[a][3]);
+        } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int c = 16 * a + 4 * g + i;
-          if (c < in_w) dx[smp * in_w + c] = dxb[a][i];
+          for (int i = 0; i < 4; ++i)
+            if (c0 + i < in_w) dx[smp * in_w + c0 + i] = dxb[a][i];
         }
+      }
     }
   }
   mlp_write_partial<INP, H, NH>(gr, in_w, part + wave * P);

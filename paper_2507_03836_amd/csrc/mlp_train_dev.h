@@ -220,32 +220,34 @@ struct MlpShapeT {
   static constexpr int TILE = TROWS * TS;
 };
 
-template <int INP, int H, int NH, typename T>
-__device__ void load_weights_lds_t(float* lds, const float* __restrict__ params, int in_w) {
+template <int INP, int H, int NH, typename T, int THREADS>
+__device__ __forceinline__ void load_weights_lds_t(float* lds, const float* __restrict__ params,
+                                                   int in_w) {
   using S = MlpShapeT<INP, H, NH>;
   T* wh = reinterpret_cast<T*>(lds + S::FLOATS);
-  for (int e = threadIdx.x; e < H * INP; e += blockDim.x) {
+  staged<H * INP, THREADS>([&](int e) {
     const int o = e / INP, i = e % INP;
     const T w = (T)((i < in_w) ? params[o * in_w + i] : 0.0f);
     wh[S::W0 + o * S::LD0 + i] = w;
     wh[S::W0T + i * S::LDH + o] = w;
-  }
+  });
   const float* p = params + H * in_w;
-  for (int e = threadIdx.x; e < H; e += blockDim.x) lds[S::B0 + e] = p[e];
+  staged<H, THREADS>([&](int e) { lds[S::B0 + e] = p[e]; });
   p += H;
+#pragma unroll
   for (int k = 1; k < NH; ++k) {
     T* wk = wh + S::WK + (k - 1) * H * S::LDH;
     T* wt = wh + S::WKT + (k - 1) * H * S::LDH;
-    for (int e = threadIdx.x; e < H * H; e += blockDim.x) {
+    staged<H * H, THREADS>([&](int e) {
       const T w = (T)p[e];
       wk[(e / H) * S::LDH + e % H] = w;
       wt[(e % H) * S::LDH + e / H] = w;
-    }
+    });
     p += H * H;
-    for (int e = threadIdx.x; e < H; e += blockDim.x) lds[S::BK + (k - 1) * H + e] = p[e];
+    staged<H, THREADS>([&](int e) { lds[S::BK + (k - 1) * H + e] = p[e]; });
     p += H;
   }
-  for (int e = threadIdx.x; e < H; e += blockDim.x) lds[S::WOUT + e] = p[e];
+  staged<H, THREADS>([&](int e) { lds[S::WOUT + e] = p[e]; });
   if (threadIdx.x == 0) lds[S::BOUT] = p[H];
 }
 
