@@ -20,10 +20,11 @@ int64_t fused_partials(int64_t n) { return fused_blocks(n, MODE_BWD); }
 
 hipError_t launch_fused_fwd(const GridDev& g, int H, int NH, const float* pos, int64_t n,
                             const void* table, fhash_dtype tdt, const float* params, float* y,
-                            hipStream_t st) {
+                            hipStream_t st, const int32_t* n_dev) {
   FusedArgs A{};
   A.pos = reinterpret_cast<const float4*>(pos);
   A.n = n;
+  A.n_dev = n_dev;
   A.table = table;
   A.params = params;
   A.y = y;

@@ -8,10 +8,11 @@ using namespace fused_detail;
 
 hipError_t launch_fused_fwd16(const GridDev& g, int H, int NH, fhash_dtype ddt, const float* pos,
                               int64_t n, const void* table, fhash_dtype tdt, const float* params,
-                              float* y, hipStream_t st) {
+                              float* y, hipStream_t st, const int32_t* n_dev) {
   FusedArgs A{};
   A.pos = reinterpret_cast<const float4*>(pos);
   A.n = n;
+  A.n_dev = n_dev;
   A.table = table;
   A.params = params;
   A.y = y;

@@ -33,6 +33,7 @@ struct FusedArgs {
   const float* target;  // MODE_TRAIN
   const float* dy;      // MODE_BWD
   int64_t n;
+  const int32_t* n_dev;  // forward: NULL, or the sample count (at most n) on the device
   const void* table;
   const float* params;
   float* y;        // MODE_FWD
@@ -165,6 +166,12 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
     fused_kernel(GridDev g, FusedArgs A) {
   constexpr int kWaves = waves_per_block(MODE);
   constexpr bool FWD = is_forward(MODE);
+  if constexpr (FWD) {
+    if (A.n_dev != nullptr) {
+      A.n = *A.n_dev;
+      if (blockIdx.x * (int64_t)(kWaves * 16) >= A.n) return;  // uniform: nothing to stage for
+    }
+  }
   constexpr bool D32 = std::is_same<D, float>::value;
   using S = MlpShape<INP, H, NH>;
   using G = GradLds<INP, H, NH>;

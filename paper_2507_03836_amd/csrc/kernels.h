@@ -38,12 +38,13 @@ hipError_t launch_mlp_bwd(int in_w, int H, int NH, const float* params, const fl
 bool fused_supported(int F, int in_w, int H, int NH);
 size_t fused_ws_bytes(int64_t n, int64_t P);
 int64_t fused_partials(int64_t n);
+// n_dev: NULL, or the device's own count of at most n samples
 hipError_t launch_fused_fwd(const GridDev& g, int H, int NH, const float* pos, int64_t n,
                             const void* table, fhash_dtype tdt, const float* params, float* y,
-                            hipStream_t st);
+                            hipStream_t st, const int32_t* n_dev = nullptr);
 hipError_t launch_fused_fwd16(const GridDev& g, int H, int NH, fhash_dtype ddt, const float* pos,
                               int64_t n, const void* table, fhash_dtype tdt, const float* params,
-                              float* y, hipStream_t st);
+                              float* y, hipStream_t st, const int32_t* n_dev = nullptr);
 hipError_t launch_fused_bwd(const GridDev& g, int H, int NH, fhash_dtype ddt, const float* pos,
                             int64_t n, const void* table, fhash_dtype tdt, const float* params,
                             const float* dy, float* d_table, float* d_params, void* ws, int64_t P,
@@ -139,6 +140,16 @@ hipError_t launch_render_march(void* ws, int W, int H, const int64_t* dims, floa
 hipError_t launch_render_composite(void* ws, int W, int H, int cur, int32_t n_alive,
                                    const float* y, const float* tf, float alpha_stop, float* rgba,
                                    int32_t* n_alive_host, hipStream_t st);
+// one device-driven iteration of a whole-image render (no host round trip)
+hipError_t launch_render_march_next(void* ws, int W, int H, const int64_t* dims, float t01,
+                                    float ds, int32_t max_steps, int32_t arm_max, int cur,
+                                    int32_t bound, float* pos_out, hipStream_t st);
+const int32_t* render_sample_count(void* ws, int W, int H);
+hipError_t launch_render_composite_next(void* ws, int W, int H, int cur, int32_t bound,
+                                        const float* y, const float* tf, float alpha_stop,
+                                        float* rgba, hipStream_t st);
+hipError_t render_progress(void* ws, int W, int H, int cur, int32_t* n_alive, int64_t* samples,
+                           int64_t* iterations, hipStream_t st);
 
 // coreset.hip: feature extraction, dilation, boxes, occupancy, coreset list
 int64_t mask_words(const int64_t* dims);

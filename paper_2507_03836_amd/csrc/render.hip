@@ -327,6 +327,27 @@ __global__ void __launch_bounds__(kMarchThreads)
   march_rays<I>(a, rays, act ? alive[i] : 0, act, out, counter, 0);
 }
 
+// One iteration of a whole-image render, driven from the device: the alive
+// count, and the pace that follows from it (Algorithm 1: rays / alive, at most
+// arm_max), are read here, so the host need not wait for the last iteration to
+// launch the next.  counters: [0], [1] alive rays of the two lists, [2] samples
+// of this iteration, then (64-bit) the samples and iterations so far.  Clears
+// the list length that the composite will append to.
+template <typename I>
+__global__ void __launch_bounds__(kMarchThreads)
+    march_next_kernel(MarchArgs a, int32_t n_rays, int32_t arm_max, Ray* __restrict__ rays,
+                      const int32_t* __restrict__ alive, float4* __restrict__ out,
+                      int32_t* __restrict__ counters, int cur) {
+  const int32_t n_alive = counters[cur];
+  if (blockIdx.x == 0 && threadIdx.x == 0) counters[1 - cur] = 0;
+  if (blockIdx.x * (int64_t)kMarchRays >= n_alive) return;  // uniform
+  const int32_t pace = n_rays / n_alive;
+  a.pace = pace > arm_max ? arm_max : pace < 1 ? 1 : pace;
+  const int64_t i = blockIdx.x * (int64_t)kMarchRays + threadIdx.x / kSteps;
+  const bool act = i < n_alive;
+  march_rays<I>(a, rays, act ? alive[i] : 0, act, out, counters + 2, 0);
+}
+
 // Several requests in one launch: request r owns the alive rays
 // [first_r, first_r + n_alive_r) of the launch's index space, with first_r a
 // multiple of kMarchRays (64 in the composite) so that every workgroup (wave)
@@ -450,6 +471,27 @@ __global__ void __launch_bounds__(256)
   composite_one(rays, act ? alive[i] : 0, act, y, tf, alpha_stop, rgba, next, n_next);
 }
 
+// The composite of a device-driven iteration: the alive count from counters
+// (march_next_kernel), which then take the iteration's samples.
+__global__ void __launch_bounds__(256)
+    composite_next_kernel(Ray* __restrict__ rays, const int32_t* __restrict__ alive,
+                          const float* __restrict__ y, const float4* __restrict__ tf,
+                          float alpha_stop, float4* __restrict__ rgba,
+                          int32_t* __restrict__ next, int32_t* __restrict__ counters, int cur) {
+  const int32_t n_alive = counters[cur];
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i == 0 && n_alive > 0) {
+    int64_t* done = reinterpret_cast<int64_t*>(counters + 4);
+    done[0] += counters[2];
+    done[1] += 1;
+    counters[2] = 0;
+  }
+  if ((i & ~(int64_t)63) >= n_alive) return;  // whole waves
+  const bool act = i < n_alive;
+  composite_one(rays, act ? alive[i] : 0, act, y, tf, alpha_stop, rgba, next,
+                counters + (1 - cur));
+}
+
 struct BatchCompReq {
   Ray* rays;
   const int32_t* alive;
@@ -508,7 +550,8 @@ size_t render_ws_bytes(int64_t NR, const int64_t* dims) {
 struct RenderWs {
   Ray* rays;
   int32_t* alive[2];
-  int32_t* counters;  // [0] n_alive of list 0, [1] of list 1, [2] sample counter
+  int32_t* counters;  // [0] n_alive of list 0, [1] of list 1, [2] sample counter, then
+                      // (device-driven renders) 64-bit samples and iterations so far
   uint64_t* occ;
 };
 
@@ -555,11 +598,8 @@ hipError_t launch_render_begin(const fhash_view* v, int W, int H, const uint64_t
   return hipStreamSynchronize(st);
 }
 
-hipError_t launch_render_march(void* ws, int W, int H, const int64_t* dims, float t01, float ds,
-                               int32_t max_steps, int32_t pace, int cur, int32_t n_alive,
-                               float* pos_out, int32_t* n_samples_host, hipStream_t st) {
-  const int64_t NR = (int64_t)W * H;
-  RenderWs w = carve(ws, NR);
+static MarchArgs march_args(const RenderWs& w, const int64_t* dims, float t01, float ds,
+                            int32_t max_steps, int32_t pace) {
   MarchArgs a;
   a.occ = w.occ;
   a.Sx = dims[0];
@@ -573,6 +613,60 @@ hipError_t launch_render_march(void* ws, int W, int H, const int64_t* dims, floa
   a.ds = ds;
   a.max_steps = max_steps;
   a.pace = pace;
+  return a;
+}
+
+// March and composite of one device-driven iteration of a whole-image render;
+// bound: alive rays at most (sizes the grids).  The decode between them reads
+// its sample count at render_sample_count(ws).
+hipError_t launch_render_march_next(void* ws, int W, int H, const int64_t* dims, float t01,
+                                    float ds, int32_t max_steps, int32_t arm_max, int cur,
+                                    int32_t bound, float* pos_out, hipStream_t st) {
+  const int64_t NR = (int64_t)W * H;
+  RenderWs w = carve(ws, NR);
+  const MarchArgs a = march_args(w, dims, t01, ds, max_steps, 1);
+  float4* out = reinterpret_cast<float4*>(pos_out);
+  auto kern = (dims[2] - 1) * (dims[1] - 1) * a.Wc < ((int64_t)1 << 31)
+                  ? march_next_kernel<int32_t>
+                  : march_next_kernel<int64_t>;
+  hipLaunchKernelGGL(kern, dim3(march_blocks(bound)), dim3(kMarchThreads), 0, st, a, (int32_t)NR,
+                     arm_max, w.rays, w.alive[cur], out, w.counters, cur);
+  return hipGetLastError();
+}
+
+const int32_t* render_sample_count(void* ws, int W, int H) {
+  return carve(ws, (int64_t)W * H).counters + 2;
+}
+
+hipError_t launch_render_composite_next(void* ws, int W, int H, int cur, int32_t bound,
+                                        const float* y, const float* tf, float alpha_stop,
+                                        float* rgba, hipStream_t st) {
+  RenderWs w = carve(ws, (int64_t)W * H);
+  hipLaunchKernelGGL(composite_next_kernel, dim3(blocks_exact(bound)), dim3(256), 0, st, w.rays,
+                     w.alive[cur], y, reinterpret_cast<const float4*>(tf), alpha_stop,
+                     reinterpret_cast<float4*>(rgba), w.alive[1 - cur], w.counters, cur);
+  return hipGetLastError();
+}
+
+// Alive rays of list cur, samples and iterations so far; synchronises st.
+hipError_t render_progress(void* ws, int W, int H, int cur, int32_t* n_alive, int64_t* samples,
+                           int64_t* iterations, hipStream_t st) {
+  RenderWs w = carve(ws, (int64_t)W * H);
+  int64_t host[4];
+  hipError_t e = hipMemcpyAsync(host, w.counters, sizeof(host), hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e != hipSuccess) return e;
+  *n_alive = reinterpret_cast<const int32_t*>(host)[cur];
+  *samples = host[2];
+  *iterations = host[3];
+  return hipSuccess;
+}
+
+hipError_t launch_render_march(void* ws, int W, int H, const int64_t* dims, float t01, float ds,
+                               int32_t max_steps, int32_t pace, int cur, int32_t n_alive,
+                               float* pos_out, int32_t* n_samples_host, hipStream_t st) {
+  RenderWs w = carve(ws, (int64_t)W * H);
+  const MarchArgs a = march_args(w, dims, t01, ds, max_steps, pace);
   hipError_t e = hipMemsetAsync(w.counters + 2, 0, 4, st);
   if (e != hipSuccess) return e;
   if (n_alive > 0) {
