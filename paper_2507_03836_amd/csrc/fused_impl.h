@@ -20,7 +20,8 @@ namespace fh {
 
 namespace fused_detail {
 
-// Waves per workgroup: eight in every mode.  The forward keeps only the
+// Waves per workgroup: at most eight in every mode, fewer (the launch decides,
+// fused_launch) where that spreads a small batch over more CUs.  The forward keeps only the
 // decoder weights in LDS; the backward modes also hold the workgroup's
 // gradient image and per-wave tiles.  MODE_FWD16: the forward with a 16-bit
 // MFMA decoder (inference).
@@ -164,12 +165,13 @@ template <int MODE, int F, typename T, int INP, int H, int NH, typename D, bool 
 __global__ void __launch_bounds__(64 * waves_per_block(MODE))
     __attribute__((amdgpu_waves_per_eu(is_forward(MODE) ? 1 : 2)))
     fused_kernel(GridDev g, FusedArgs A) {
-  constexpr int kWaves = waves_per_block(MODE);
+  constexpr int kWaves = waves_per_block(MODE);  // of LDS; blockDim.x / 64 of them run
+  const int nw = blockDim.x >> 6;
   constexpr bool FWD = is_forward(MODE);
   if constexpr (FWD) {
     if (A.n_dev != nullptr) {
       A.n = *A.n_dev;
-      if (blockIdx.x * (int64_t)(kWaves * 16) >= A.n) return;  // uniform: nothing to stage for
+      if (blockIdx.x * (int64_t)(nw * 16) >= A.n) return;  // uniform: nothing to stage for
     }
   }
   constexpr bool D32 = std::is_same<D, float>::value;
@@ -184,12 +186,19 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
                            : train_wave_scratch_t<INP, H, NH>();
   __shared__ __attribute__((aligned(16))) float lds[WFL + GFL + kWaves * WS + 1];
   __shared__ LevelDev lv[FHASH_MAX_LEVELS];
-  if constexpr (MODE == MODE_FWD16)
-    load_weights_lds_h<INP, H, NH, D, 64 * kWaves>(lds, A.params, A.in_w);
-  else if constexpr (D32)
-    load_weights_lds<INP, H, NH, 64 * kWaves>(lds, A.params, A.in_w);
+  auto stage = [&](auto threads) {
+    constexpr int N = decltype(threads)::value;
+    if constexpr (MODE == MODE_FWD16)
+      load_weights_lds_h<INP, H, NH, D, N>(lds, A.params, A.in_w);
+    else if constexpr (D32)
+      load_weights_lds<INP, H, NH, N>(lds, A.params, A.in_w);
+    else
+      load_weights_lds_t<INP, H, NH, D, N>(lds, A.params, A.in_w);
+  };
+  if (nw == kWaves)
+    stage(std::integral_constant<int, 64 * kWaves>());
   else
-    load_weights_lds_t<INP, H, NH, D, 64 * kWaves>(lds, A.params, A.in_w);
+    stage(std::integral_constant<int, 0>());
   float* grad = lds + WFL;
   if constexpr (!FWD) grad_lds_zero<INP, H, NH>(grad);
   for (int e = threadIdx.x; e < FHASH_MAX_LEVELS; e += blockDim.x) lv[e] = g.lv[e];
@@ -199,8 +208,8 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
   const int wib = threadIdx.x >> 6;
   float* scratch = lds + WFL + GFL + wib * WS;
   const int64_t nblk = (A.n + 15) / 16;
-  const int64_t nwav = (int64_t)gridDim.x * kWaves;
-  const int64_t wave = (int64_t)blockIdx.x * kWaves + wib;
+  const int64_t nwav = (int64_t)gridDim.x * nw;
+  const int64_t wave = (int64_t)blockIdx.x * nw + wib;
   double loss = 0.0;
   for (int64_t b = wave; b < nblk; b += nwav) {
     // Keep the decoder weights in LDS rather than in registers across blocks:
@@ -251,19 +260,26 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
   }
 }
 
-inline int64_t fused_waves(int64_t n, int mode) {
-  const int kWaves = waves_per_block(mode);
-  int64_t nblk = (n + 15) / 16;
-  int64_t cap = is_forward(mode) ? 8192 : 2048;
-  int64_t w = nblk < cap ? nblk : cap;
-  w = ((w + kWaves - 1) / kWaves) * kWaves;
-  return w < kWaves ? kWaves : w;
+// Workgroups of a launch (= decoder-gradient partials of a backward launch) and
+// waves of each.  A wave takes one block of 16 samples where the waves allow
+// (8192 in the forward, 2048 in the backward).  Eight waves share a workgroup's
+// weights and gradient image; a batch of fewer than 2048 blocks spreads over 256
+// workgroups first, a CU each: the lookups of 16 samples are about 4,000 line
+// requests, one per cycle and CU, so eight waves on one CU and 248 CUs idle
+// waited for each other.  1000 points, 8 waves on 8 CUs / a wave on each of 63:
+// 33.1 / 23.2 us, 19.1 with the weights staged in one latency.
+struct FusedLaunch {
+  int64_t blocks;
+  int waves;
+};
+inline FusedLaunch fused_launch(int64_t n, int mode) {
+  const int64_t nblk = n > 0 ? (n + 15) / 16 : 1, cap = is_forward(mode) ? 8192 : 2048;
+  const int64_t w = nblk < cap ? nblk : cap;
+  const int64_t most = waves_per_block(mode), each = (w + 255) / 256;
+  const int64_t waves = each < most ? each : most;
+  return {(w + waves - 1) / waves, (int)waves};
 }
-
-// Workgroups of a launch (= decoder-gradient partials of a backward launch).
-inline int64_t fused_blocks(int64_t n, int mode) {
-  return fused_waves(n, mode) / waves_per_block(mode);
-}
+inline int64_t fused_blocks(int64_t n, int mode) { return fused_launch(n, mode).blocks; }
 
 // The brick slot order is built for the production decoder shapes only
 // (32 inputs, hidden width 64, 2 or 3 hidden layers, F = 2 or 4); the host
@@ -275,17 +291,15 @@ constexpr bool brick_shape() {
 
 template <int MODE, int F, typename T, int INP, int H, int NH, typename D>
 hipError_t fused_t(const GridDev& g, FusedArgs A, float* d_params, hipStream_t st) {
-  constexpr int kWaves = waves_per_block(MODE);
-  const int64_t nb = fused_blocks(A.n, MODE);
+  const FusedLaunch fl = fused_launch(A.n, MODE);
+  const dim3 grid((unsigned)fl.blocks), block(64 * fl.waves);
   if (g.lv[0].brick) {
     if constexpr (brick_shape<F, INP, H, NH>())
-      hipLaunchKernelGGL((fused_kernel<MODE, F, T, INP, H, NH, D, true>), dim3((unsigned)nb),
-                         dim3(64 * kWaves), 0, st, g, A);
+      hipLaunchKernelGGL((fused_kernel<MODE, F, T, INP, H, NH, D, true>), grid, block, 0, st, g, A);
     else
       return hipErrorNotSupported;
   } else {
-    hipLaunchKernelGGL((fused_kernel<MODE, F, T, INP, H, NH, D, false>), dim3((unsigned)nb),
-                       dim3(64 * kWaves), 0, st, g, A);
+    hipLaunchKernelGGL((fused_kernel<MODE, F, T, INP, H, NH, D, false>), grid, block, 0, st, g, A);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || is_forward(MODE)) return e;
@@ -294,7 +308,7 @@ hipError_t fused_t(const GridDev& g, FusedArgs A, float* d_params, hipStream_t s
                               A.d_table, st);
     if (e != hipSuccess) return e;
   }
-  return launch_reduce_partials(A.part, nb, A.P, d_params, st);
+  return launch_reduce_partials(A.part, fl.blocks, A.P, d_params, st);
 }
 
 template <int MODE, int F, typename T, typename D>

@@ -44,43 +44,79 @@ struct MlpShape {
   static constexpr int SCRATCH = 2 * TILE;
 };
 
-// for e in [0, N) step THREADS from the thread's index, unrolled: a workgroup of
-// THREADS stages an array whose loads are all in flight before the first is
-// stored.  (With a loop over blockDim.x every load was waited for, 12 to 40
-// latencies in a chain: mlp_fwd_kernel<64, 64, 2> on 100,003 samples took 54 us,
-// so and with float4 inputs 39.)
-template <int N, int THREADS, typename Fn>
-__device__ __forceinline__ void staged(Fn fn) {
-  constexpr int FULL = N / THREADS;
+// A thread's share of N values, elements threadIdx.x + k T of a workgroup of T =
+// THREADS threads (or of any whole waves, THREADS = 0).  Loading every part of
+// the decoder before the first store keeps one latency between a workgroup and
+// its weights; with a loop over blockDim.x every load was waited for, 12 to 40
+// latencies in a chain (mlp_fwd_kernel<64, 64, 2> on 100,003 samples 54 us, so
+// and with float4 inputs 28).
+template <int N, int THREADS>
+struct Staged {
+  static constexpr int K = (N + (THREADS > 0 ? THREADS : 64) - 1) / (THREADS > 0 ? THREADS : 64);
+  float v[K];
+  static __device__ __forceinline__ int at(int k) {
+    return k * (THREADS > 0 ? THREADS : (int)blockDim.x) + (int)threadIdx.x;
+  }
+  static __device__ __forceinline__ bool has(int k) {
+    return (THREADS > 0 && N % THREADS == 0) || at(k) < N;
+  }
+  template <typename Fn>
+  __device__ __forceinline__ void load(Fn fn) {
 #pragma unroll
-  for (int k = 0; k < FULL; ++k) fn(k * THREADS + (int)threadIdx.x);
-  if constexpr (N % THREADS != 0)
-    if (FULL * THREADS + (int)threadIdx.x < N) fn(FULL * THREADS + (int)threadIdx.x);
-}
+    for (int k = 0; k < K; ++k)
+      if (has(k)) v[k] = fn(at(k));
+  }
+  template <typename Fn>
+  __device__ __forceinline__ void store(Fn fn) const {
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (has(k)) fn(at(k), v[k]);
+  }
+};
 
-// Copy the packed parameter vector into the LDS weight image (zero-padding the
-// input columns of W0 beyond in_w).  Whole workgroup of THREADS; caller syncs.
+// The packed parameter vector in a workgroup's registers: W_0 [H][in_w] (padded
+// to INP columns with zeros), b_0, then W_k, b_k, the output weights and bias.
+template <int INP, int H, int NH, int THREADS>
+struct StagedMlp {
+  static constexpr int NK = NH > 1 ? NH - 1 : 1;
+  Staged<H * INP, THREADS> w0;
+  Staged<H, THREADS> b0, bk[NK], wout;
+  Staged<H * H, THREADS> wk[NK];
+  float bout;
+  __device__ __forceinline__ StagedMlp(const float* __restrict__ params, int in_w) {
+    w0.load([&](int e) { return e % INP < in_w ? params[e / INP * in_w + e % INP] : 0.0f; });
+    const float* p = params + H * in_w;
+    b0.load([&](int e) { return p[e]; });
+    p += H;
+#pragma unroll
+    for (int k = 0; k < NH - 1; ++k) {
+      wk[k].load([&](int e) { return p[e]; });
+      p += H * H;
+      bk[k].load([&](int e) { return p[e]; });
+      p += H;
+    }
+    wout.load([&](int e) { return p[e]; });
+    bout = p[H];
+  }
+};
+
+// Copy the packed parameter vector into the LDS weight image.  Whole workgroup
+// (THREADS: Staged); caller syncs.
 template <int INP, int H, int NH, int THREADS>
 __device__ __forceinline__ void load_weights_lds(float* lds, const float* __restrict__ params,
                                                  int in_w) {
   using S = MlpShape<INP, H, NH>;
-  staged<H * INP, THREADS>([&](int e) {
-    const int o = e / INP, i = e % INP;
-    lds[S::W0 + o * S::LD0 + i] = (i < in_w) ? params[o * in_w + i] : 0.0f;
-  });
-  const float* p = params + H * in_w;
-  staged<H, THREADS>([&](int e) { lds[S::B0 + e] = p[e]; });
-  p += H;
+  const StagedMlp<INP, H, NH, THREADS> m(params, in_w);
+  m.w0.store([&](int e, float v) { lds[S::W0 + e / INP * S::LD0 + e % INP] = v; });
+  m.b0.store([&](int e, float v) { lds[S::B0 + e] = v; });
 #pragma unroll
-  for (int k = 1; k < NH; ++k) {
-    float* wk = lds + S::WK + (k - 1) * S::WKSTRIDE;
-    staged<H * H, THREADS>([&](int e) { wk[(e / H) * S::LDH + e % H] = p[e]; });
-    p += H * H;
-    staged<H, THREADS>([&](int e) { wk[H * S::LDH + e] = p[e]; });
-    p += H;
+  for (int k = 0; k < NH - 1; ++k) {
+    float* wk = lds + S::WK + k * S::WKSTRIDE;
+    m.wk[k].store([&](int e, float v) { wk[(e / H) * S::LDH + e % H] = v; });
+    m.bk[k].store([&](int e, float v) { wk[H * S::LDH + e] = v; });
   }
-  staged<H, THREADS>([&](int e) { lds[S::WOUT + e] = p[e]; });
-  if (threadIdx.x == 0) lds[S::BOUT] = p[H];
+  m.wout.store([&](int e, float v) { lds[S::WOUT + e] = v; });
+  if (threadIdx.x == 0) lds[S::BOUT] = m.bout;
 }
 
 // out = act(W in + b) for one 16-sample block.  W is [HB*16][ld] in LDS.
@@ -290,30 +326,24 @@ struct MlpShapeH {
   static constexpr int TOTAL_FLOATS = FLOATS + (HALVES + 1) / 2 + 4;
 };
 
-// Round the packed FP32 parameters into the 16-bit LDS image (RNE; W0 columns
-// beyond in_w are zero).  Whole workgroup of THREADS; caller syncs.
+// Round the packed FP32 parameters into the 16-bit LDS image (RNE).  Whole
+// workgroup (THREADS: Staged); caller syncs.
 template <int INP, int H, int NH, typename T, int THREADS>
 __device__ __forceinline__ void load_weights_lds_h(float* lds, const float* __restrict__ params,
                                                    int in_w) {
   using S = MlpShapeH<INP, H, NH>;
   T* wh = reinterpret_cast<T*>(lds + S::FLOATS);
-  staged<H * INP, THREADS>([&](int e) {
-    const int o = e / INP, i = e % INP;
-    wh[S::W0 + o * S::LD0 + i] = (T)((i < in_w) ? params[o * in_w + i] : 0.0f);
-  });
-  const float* p = params + H * in_w;
-  staged<H, THREADS>([&](int e) { lds[S::B0 + e] = p[e]; });
-  p += H;
+  const StagedMlp<INP, H, NH, THREADS> m(params, in_w);
+  m.w0.store([&](int e, float v) { wh[S::W0 + e / INP * S::LD0 + e % INP] = (T)v; });
+  m.b0.store([&](int e, float v) { lds[S::B0 + e] = v; });
 #pragma unroll
-  for (int k = 1; k < NH; ++k) {
-    T* wk = wh + S::WK + (k - 1) * H * S::LDH;
-    staged<H * H, THREADS>([&](int e) { wk[(e / H) * S::LDH + e % H] = (T)p[e]; });
-    p += H * H;
-    staged<H, THREADS>([&](int e) { lds[S::BK + (k - 1) * H + e] = p[e]; });
-    p += H;
+  for (int k = 0; k < NH - 1; ++k) {
+    T* wk = wh + S::WK + k * H * S::LDH;
+    m.wk[k].store([&](int e, float v) { wk[(e / H) * S::LDH + e % H] = (T)v; });
+    m.bk[k].store([&](int e, float v) { lds[S::BK + k * H + e] = v; });
   }
-  staged<H, THREADS>([&](int e) { lds[S::WOUT + e] = p[e]; });
-  if (threadIdx.x == 0) lds[S::BOUT] = p[H];
+  m.wout.store([&](int e, float v) { lds[S::WOUT + e] = v; });
+  if (threadIdx.x == 0) lds[S::BOUT] = m.bout;
 }
 
 // out = relu(W round(in) + b) with 16-bit operands and FP32 accumulation.

@@ -225,30 +225,24 @@ __device__ __forceinline__ void load_weights_lds_t(float* lds, const float* __re
                                                    int in_w) {
   using S = MlpShapeT<INP, H, NH>;
   T* wh = reinterpret_cast<T*>(lds + S::FLOATS);
-  staged<H * INP, THREADS>([&](int e) {
-    const int o = e / INP, i = e % INP;
-    const T w = (T)((i < in_w) ? params[o * in_w + i] : 0.0f);
-    wh[S::W0 + o * S::LD0 + i] = w;
-    wh[S::W0T + i * S::LDH + o] = w;
+  const StagedMlp<INP, H, NH, THREADS> m(params, in_w);
+  m.w0.store([&](int e, float v) {
+    wh[S::W0 + e / INP * S::LD0 + e % INP] = (T)v;
+    wh[S::W0T + e % INP * S::LDH + e / INP] = (T)v;
   });
-  const float* p = params + H * in_w;
-  staged<H, THREADS>([&](int e) { lds[S::B0 + e] = p[e]; });
-  p += H;
+  m.b0.store([&](int e, float v) { lds[S::B0 + e] = v; });
 #pragma unroll
-  for (int k = 1; k < NH; ++k) {
-    T* wk = wh + S::WK + (k - 1) * H * S::LDH;
-    T* wt = wh + S::WKT + (k - 1) * H * S::LDH;
-    staged<H * H, THREADS>([&](int e) {
-      const T w = (T)p[e];
-      wk[(e / H) * S::LDH + e % H] = w;
-      wt[(e % H) * S::LDH + e / H] = w;
+  for (int k = 0; k < NH - 1; ++k) {
+    T* wk = wh + S::WK + k * H * S::LDH;
+    T* wt = wh + S::WKT + k * H * S::LDH;
+    m.wk[k].store([&](int e, float v) {
+      wk[(e / H) * S::LDH + e % H] = (T)v;
+      wt[(e % H) * S::LDH + e / H] = (T)v;
     });
-    p += H * H;
-    staged<H, THREADS>([&](int e) { lds[S::BK + (k - 1) * H + e] = p[e]; });
-    p += H;
+    m.bk[k].store([&](int e, float v) { lds[S::BK + k * H + e] = v; });
   }
-  staged<H, THREADS>([&](int e) { lds[S::WOUT + e] = p[e]; });
-  if (threadIdx.x == 0) lds[S::BOUT] = p[H];
+  m.wout.store([&](int e, float v) { lds[S::WOUT + e] = v; });
+  if (threadIdx.x == 0) lds[S::BOUT] = m.bout;
 }
 
 // Forward of one block through the 16-bit decoder, keeping the (FP32) hidden
