@@ -135,6 +135,100 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// The value of lane 7 - q of the caller's 8 lanes (DPP half-row mirror).
+__device__ __forceinline__ f4v mirror8(const f4v x) {
+  f4v r;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    r[c] = __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(x[c]), 0x141, 0xF, 0xF, false));
+  return r;
+}
+
+// The sweep over the layout with the moments beside the parameters, `blocks`
+// whole blocks of 16 parameters (pm: 16 p then 16 m; gv: 16 g then 16 v).  Read
+// array by array (adam_kernel) every access covers half of each 128-byte line:
+// 68.7 M parameters took 550 us (non-temporal), or 427 with ordinary accesses,
+// which however took the caches from the kernels around the sweep (the next
+// step's sampler and mark 40 us slower).  Here 8 lanes read a whole line (lane
+// q < 4: values 4q.., lane 7 - q: their moments) of two blocks, hand each other
+// the halves they miss, so that lane q < 4 steps 4 parameters of the first block
+// and lane 7 - q of the second, and hand them back: 480 us writing the moments'
+// half of [g | v] lines alone, 344 us (6.4 TB/s) writing them whole, with the
+// gradient's reset.  The 4 gradient lanes of a block read its touched flag in one
+// instruction before one of them clears it.
+__global__ void __launch_bounds__(256)
+    adam_runs_kernel(AdamK k, f4v* __restrict__ pm, f4v* __restrict__ gv,
+                     void* __restrict__ shadow, int sdt, int64_t blocks, int64_t first,
+                     const int32_t* __restrict__ found_inf, uint8_t* __restrict__ touch,
+                     int64_t tb, int64_t te) {
+  constexpr int kPairs = 2;  // pairs of blocks per 8 lanes in flight
+  const bool skip = found_inf != nullptr && *found_inf != 0;
+  const int q = threadIdx.x & 7;
+  const bool lo = q < 4;
+  const int chunk = lo ? q : 7 - q;         // the lane's 4 of the 16 parameters
+  const int at = lo ? chunk : 4 + chunk;    // float4 of a block's 8
+  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
+  const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  const f4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  // whole waves run the same iterations: the exchanges need every lane
+  for (int64_t b0 = wave * 16 * kPairs; b0 < blocks; b0 += waves * 16 * kPairs) {
+    f4v P[kPairs][2], G[kPairs][2];
+    int64_t blk[kPairs][2];
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int64_t b = b0 + 16 * u + 8 * h + ((threadIdx.x & 63) >> 3);
+        blk[u][h] = b < blocks ? b : -1;
+        P[u][h] = G[u][h] = zero;
+        if (b >= blocks) continue;
+        if (!skip) P[u][h] = __builtin_nontemporal_load(pm + b * 8 + at);
+        bool read = !skip;  // v
+        if (lo) {           // g: only where the segment was written
+          const int64_t f = first + 16 * b + 4 * chunk;
+          read = true;
+          if (touch != nullptr && f >= tb && f < te) {
+            const int64_t seg = f / FHASH_TOUCH_FLOATS;
+            read = f + 4 > te || touch[seg] != 0;
+            if (f % FHASH_TOUCH_FLOATS == 0) touch[seg] = 0;
+          }
+        }
+        if (read) G[u][h] = __builtin_nontemporal_load(gv + b * 8 + at);
+      }
+#pragma unroll
+    for (int u = 0; u < kPairs; ++u) {
+      const int64_t A = blk[u][0], B = blk[u][1], own = lo ? A : B;
+      const f4v rp = mirror8(lo ? P[u][1] : P[u][0]), rg = mirror8(lo ? G[u][1] : G[u][0]);
+      f4v p = lo ? P[u][0] : rp, m = lo ? rp : P[u][1];
+      const f4v g = lo ? G[u][0] : rg;
+      f4v v = lo ? rg : G[u][1];
+      if (!skip) {
+        adam4(k, g, p, m, v);
+        const f4v bp = mirror8(lo ? m : p), bv = mirror8(v);
+        if (A >= 0) {
+          __builtin_nontemporal_store(lo ? p : bp, pm + A * 8 + at);
+          __builtin_nontemporal_store(lo ? zero : bv, gv + A * 8 + at);
+        }
+        if (B >= 0) {
+          __builtin_nontemporal_store(lo ? bp : m, pm + B * 8 + at);
+          __builtin_nontemporal_store(lo ? zero : v, gv + B * 8 + at);
+        }
+        if (shadow != nullptr && own >= 0)
+          store_shadow4(shadow, sdt, (first + 16 * own) / 4 + chunk, p);
+      }
+      if (skip && lo) {  // a skipped step only resets the gradient
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const f4v x = G[u][h];
+          if (blk[u][h] >= 0 && (x[0] != 0.0f || x[1] != 0.0f || x[2] != 0.0f || x[3] != 0.0f))
+            __builtin_nontemporal_store(zero, gv + blk[u][h] * 8 + at);
+        }
+      }
+    }
+  }
+}
+
 __global__ void __launch_bounds__(256)
     check_finite_kernel(const float* __restrict__ g, int64_t n, int32_t* __restrict__ found) {
   int bad = 0;
@@ -242,6 +336,19 @@ hipError_t launch_adam(const fhash_adam_desc* o, float* p, float* g, float* m, f
   if (b < 1) b = 1;
   uint8_t* tf = touch ? touch->flags : nullptr;
   const int64_t tb = touch ? touch->begin : 0, te = touch ? touch->end : 0;
+  if (o->moments == FHASH_MOMENTS_WITH_PARAMS && first % 16 == 0 && n >= 16) {
+    // whole blocks through the line-wise sweep, what is left of the last below
+    const int64_t blocks = n / 16;
+    int64_t w = (blocks + 127) / 128;  // 4 waves of 32 blocks
+    if (w > 131072) w = 131072;
+    hipLaunchKernelGGL(adam_runs_kernel, dim3((unsigned)w), dim3(256), 0, st, k,
+                       reinterpret_cast<f4v*>(p + 2 * first), reinterpret_cast<f4v*>(g + 2 * first),
+                       shadow, (int)sdt, blocks, first, found_inf, tf, tb, te);
+    first += 16 * blocks;
+    n -= 16 * blocks;
+    if (n == 0) return hipGetLastError();
+    b = 1;
+  }
   // moments with parameters: p, g (and m, v) in runs of 16; paired: m, v only
   const int64_t pm = o->moments == FHASH_MOMENTS_WITH_PARAMS ? ~(int64_t)15 : 0;
   if (o->moments != FHASH_MOMENTS_SEPARATE)
