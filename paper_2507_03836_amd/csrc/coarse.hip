@@ -14,6 +14,8 @@
 // The sum over samples is the adjoint of the quadrilinear blend (Sec. 3.2.3),
 // reordered: the same result up to FP32 summation order.
 #include <climits>
+#include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "encode_dev.h"
@@ -52,6 +54,21 @@ __device__ __forceinline__ int64_t vertex_slot(const LevelDev& d, const ulonglon
   const int32_t tz = t * d.rz + z;
   const ulonglong2 e = dir[d.dir_off + (int64_t)((tz * d.wv + (x >> 6)) * d.ry + y)];
   return entry_slot(e, x & 63, d.slot_off, valid);
+}
+
+// The value lane K of the caller's row of 16 lanes holds.
+template <int K>
+__device__ __forceinline__ int row_get(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, 0x150 + K, 0xF, 0xF, false);
+}
+template <int K>
+__device__ __forceinline__ float row_get(float x) {
+  return __int_as_float(row_get<K>(__float_as_int(x)));
+}
+
+template <typename Fn, int... U>
+__device__ __forceinline__ void each(Fn& fn, std::integer_sequence<int, U...>) {
+  (fn(std::integral_constant<int, U>{}), ...);
 }
 
 // Adds the F values of run to the vertex's floats at `at` in LDS (8-byte aligned
@@ -183,9 +200,19 @@ __global__ void __launch_bounds__(kThreads)
       // registers while its vertex stays the same (neighbours in a sorted batch
       // often share the cell), so an LDS add is issued per change of vertex.  The
       // four groups of a wave walk runs far apart, so that they seldom add to the
-      // same vertex at once (510 -> 499 us)
+      // same vertex at once (510 -> 499 us).  Lane c of a group locates sample c
+      // of the next 16 and the samples are handed round by row broadcasts, for
+      // every lane of the group locating each sample: 499 -> 457 us (2^18 samples,
+      // five levels: 132 -> 117)
       const int cr = tid & 15;
-      const int ox = cr & 1, oy = (cr >> 1) & 1, oz = (cr >> 2) & 1, ot = (cr >> 3) & 1;
+      // weight of the corner along an axis: f or 1 - f as f * sgn + one
+      const float sx = cr & 1 ? 1.0f : -1.0f, qx = cr & 1 ? 0.0f : 1.0f;
+      const float sy = cr & 2 ? 1.0f : -1.0f, qy = cr & 2 ? 0.0f : 1.0f;
+      const float sz = cr & 4 ? 1.0f : -1.0f, qz = cr & 4 ? 0.0f : 1.0f;
+      const float st = cr & 8 ? 1.0f : -1.0f, qt = cr & 8 ? 0.0f : 1.0f;
+      const int ny = ext[0], nz = ny * ext[1], nt = nz * ext[2];  // box strides
+      const int corner =
+          (cr & 1) + (cr & 2 ? ny : 0) + (cr & 4 ? nz : 0) + (cr & 8 ? nt : 0);
       constexpr int kGroups = kThreads / 16;
       const int per = (bn + kGroups - 1) / kGroups;
       const int ib = (((tid >> 4) & 3) * (kGroups / 4) + wid) * per, ie = min(bn, ib + per);
@@ -193,38 +220,37 @@ __global__ void __launch_bounds__(kThreads)
       float run[F];
 #pragma unroll
       for (int k = 0; k < F; ++k) run[k] = 0.0f;
-      for (int i0 = ib; i0 < ie; i0 += kUnroll) {
-        float4 pu[kUnroll];
-        float gu[kUnroll][F];
+      for (int j0 = 0; j0 < per; j0 += 16) {  // the same trips in every lane
+        const int i = ib + j0 + cr;
+        const bool mine = i < ie;
+        Cell c = {};
+        float gr[F];
+        if (mine) c = locate_cell(d, pos[s0 + i]);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          const int i = i0 + u;
-          pu[u] = i < ie ? pos[s0 + i] : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int k = 0; k < F; ++k) gr[k] = mine ? gl[(s0 + i) * sample_step + k] : 0.0f;
+        const int at = mine ? (c.x - blo[0]) + (c.y - blo[1]) * ny + (c.z - blo[2]) * nz +
+                                  (c.t - blo[3]) * nt
+                            : -1;
+        auto sample = [&](auto u) {  // sample j0 + u of the group's run
+          constexpr int U = decltype(u)::value;
+          if (j0 + U >= per) return;
+          const int a = row_get<U>(at);
+          const float w = (fmaf(row_get<U>(c.fx), sx, qx) * fmaf(row_get<U>(c.fy), sy, qy)) *
+                          (fmaf(row_get<U>(c.fz), sz, qz) * fmaf(row_get<U>(c.ft), st, qt));
+          float gu[F];
 #pragma unroll
-          for (int k = 0; k < F; ++k) gu[u][k] = i < ie ? gl[(s0 + i) * sample_step + k] : 0.0f;
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          if (i0 + u >= ie) break;
-          int cx, cy, cz, ct;
-          float fx, fy, fz, ft;
-          locate(pu[u].x, d.rx, d.sx, cx, fx);
-          locate(pu[u].y, d.ry, d.sy, cy, fy);
-          locate(pu[u].z, d.rz, d.sz, cz, fz);
-          locate(pu[u].w, d.rt, d.st, ct, ft);
-          const float w = ((ox ? fx : 1.0f - fx) * (oy ? fy : 1.0f - fy)) *
-                          ((oz ? fz : 1.0f - fz) * (ot ? ft : 1.0f - ft));
-          const int li = (((ct + ot - blo[3]) * ext[2] + (cz + oz - blo[2])) * ext[1] +
-                          (cy + oy - blo[1])) * ext[0] + (cx + ox - blo[0]);
-          if (li != cur) {
+          for (int k = 0; k < F; ++k) gu[k] = row_get<U>(gr[k]);
+          const int li = a + corner;
+          if (a >= 0 && li != cur) {
             if (cur >= 0) lds_add<F>(acc + cur * F, run);
             cur = li;
 #pragma unroll
             for (int k = 0; k < F; ++k) run[k] = 0.0f;
           }
 #pragma unroll
-          for (int k = 0; k < F; ++k) run[k] += w * gu[u][k];
-        }
+          for (int k = 0; k < F; ++k) run[k] += w * gu[k];
+        };
+        each(sample, std::make_integer_sequence<int, 16>{});
       }
       if (cur >= 0) lds_add<F>(acc + cur * F, run);
       __syncthreads();
@@ -301,9 +327,12 @@ __global__ void __launch_bounds__(kThreads)
 template <int F>
 hipError_t launch_f(const GridDev& g, const float* pos, int64_t n, const float* grad,
                     int64_t level_step, int64_t sample_step, float* d_table, hipStream_t st) {
-  // about two workgroups per CU: a short batch in shorter chunks
+  // at least a workgroup per CU: a short batch in shorter chunks.  Each clears and
+  // adds a box of its own, so shorter ones than that cost more (65,537 samples,
+  // four levels: 24.8 us in 130 workgroups, 30.6 in 258, 42.4 in 514; 2^18, five
+  // levels: 117 in 640, 134 in 1,280, 157 in 2,560)
   int chunk = kChunk;
-  while (chunk > kChunkMin && (n + chunk - 1) / chunk * g.coarse < 512) chunk /= 2;
+  while (chunk > kChunkMin && (n + chunk - 1) / chunk * g.coarse < 256) chunk /= 2;
   const int64_t blocks = (n + chunk - 1) / chunk;
   hipLaunchKernelGGL(coarse_scatter_kernel<F>, dim3((unsigned)blocks, (unsigned)g.coarse),
                      dim3(kThreads), kCap * sizeof(float), st, g,
