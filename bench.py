@@ -178,9 +178,9 @@ def parse():
                          "summing it in LDS per chunk of the batch before its atomics "
                          "(FHASH_COARSE_LDS, the default)")
     ap.add_argument("--sort-reduce", action="store_true",
-                    help="with sorted batches: at the coarse levels, sum a corner across the "
-                         "samples of a scatter instruction before one atomic when they all "
-                         "share its slot (FHASH_SAMPLES_SORTED)")
+                    help="with sorted batches: declare the order to the fused step "
+                         "(FHASH_SAMPLES_SORTED), which sums the coarse levels in LDS also "
+                         "with --no-coarse-lds")
     ap.add_argument("--field-seed", type=int, default=1002)
     ap.add_argument("--sampler-seed", type=int, default=2002)
     ap.add_argument("--psnr-target", type=float, default=0.0,
@@ -1063,11 +1063,13 @@ def _to_psnr(model, step, k_done, t_first, ppos, ptgt, target, eval_every, max_s
 
 
 def coarse_levels(res, n):
-    """Levels that FHASH_COARSE_LDS sends through the LDS scatter: from the
-    coarsest on, those with at most one cell per sample of the batch."""
+    """Levels of two features that FHASH_COARSE_LDS sends through the LDS
+    scatter: from the coarsest on, those with at most two cells per sample of
+    the batch (smaller batches: or at most 8000 and n vertices)."""
     lc = 0
     for r in res:
-        if (r[0] - 1) * (r[1] - 1) * (r[2] - 1) * (r[3] - 1) > n:
+        if ((r[0] - 1) * (r[1] - 1) * (r[2] - 1) * (r[3] - 1) > 2 * n
+                and r[0] * r[1] * r[2] * r[3] > min(8000, n)):
             break
         lc += 1
     return lc
@@ -1333,7 +1335,7 @@ def headline_bench(args):
     alg = (3092 if reads16 else 4116) * B
     comp = mx["compulsory"]["bytes"]
     # with FHASH_COARSE_LDS the fused kernel issues the requests of the levels
-    # with more than one cell per sample only; the coarse levels' requests are
+    # with more than two cells per sample only; the coarse levels' requests are
     # replaced by one per touched vertex row segment of a chunk's LDS box
     # (the library takes the LDS path on row-ordered indexes only)
     lc = coarse_levels(cfg.res, B) if args.coarse_lds and args.layout == "rows" else 0
@@ -1570,7 +1572,7 @@ def main():
                                 + "-".join(map(str, cfg.width))
                                 + f", batch 2^{int(np.log2(B))} coreset draws"
                                 + (", Morton-sorted batches" if args.sort else "")
-                                + (" with equal slots merged before the atomics" if args.sort and
+                                + (" declared to the fused step" if args.sort and
                                    args.sort_reduce else "")
                                 + (", dense index (every box vertex)" if args.dense_index
                                    else "")

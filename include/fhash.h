@@ -278,17 +278,18 @@ int fhash_fused_fwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
  * of 16 floats separated by 16-float gaps (gradient value i at
  * d_table[i + 16 floor(i / 16)]; the gradient array of the optimiser layout
  * FHASH_MOMENTS_WITH_PARAMS below); the table read is independent of it
- * (table_dt).  FHASH_COARSE_LDS: the levels with at most one cell per
- * sample of the batch (0 .. lc - 1, coarsest first; row-ordered indexes only,
- * ignored on brick-ordered ones) are not added by the fused kernel: their
+ * (table_dt).  FHASH_COARSE_LDS: the levels with at most two cells per
+ * sample of the batch (one for more than two features; 0 .. lc - 1, coarsest
+ * first; row-ordered indexes only, ignored on brick-ordered ones) are not added by the fused kernel: their
  * encoding gradient goes to the workspace, and a second kernel on the same
- * stream sums it per chunk of 2048 consecutive samples into an LDS image of
+ * stream sums it per chunk of up to 2048 consecutive samples into an LDS image of
  * the vertex box the chunk touches and adds that box with one atomic per
  * touched vertex and feature (a chunk whose box exceeds 16000 floats is taken
  * in 4 parts, and a part that still exceeds it adds its samples directly).
  * Sorted batches give compact boxes; the results are the same up to FP32
  * summation order.  The workspace then grows by lc x n x F floats (the size
- * query includes it).  Other bits: FHASH_EINVAL.  touch: NULL, or segment
+ * query includes it).  Without either flag the coarsest levels of at most n
+ * vertices and 16000 floats take the same path.  Other bits: FHASH_EINVAL.  touch: NULL, or segment
  * flags of d_table to set, by logical float index (see fhash_touch). */
 #define FHASH_SAMPLES_SORTED 1u
 #define FHASH_GRAD_PAIRED 2u
@@ -550,9 +551,9 @@ int fhash_sample(uint64_t seed, uint64_t step, int64_t n, const uint64_t* corese
 /* Reorder a batch of samples (pos float4[n], target float[n] or NULL, both
  * device, in place) by a 4D Morton key of the positions quantised to 256
  * cells per axis (stable LSD radix sort).  Samples of the same cells become
- * neighbours, which the gathers and the merge of equal slots before the
- * scatter-add's atomics (FHASH_SAMPLES_SORTED) exploit; the MSE loss and its gradient do not depend on the
- * order.  ws: device workspace (query with ws == NULL); n < 2^31. */
+ * neighbours, which the gathers, the scatter-add's atomics and the LDS sums of
+ * the coarse levels (FHASH_SAMPLES_SORTED) exploit; the MSE loss and its
+ * gradient do not depend on the order.  ws: device workspace (query with ws == NULL); n < 2^31. */
 int fhash_sort_samples(float* pos, float* target, int64_t n, void* ws, size_t* ws_bytes,
                        void* stream);
 
