@@ -199,6 +199,7 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
     stage(std::integral_constant<int, 64 * kWaves>());
   else
     stage(std::integral_constant<int, 0>());
+  static_assert(WFL % 4 == 0, "the gradient image is read 16 bytes at a time");
   float* grad = lds + WFL;
   if constexpr (!FWD) grad_lds_zero<INP, H, NH>(grad);
   for (int e = threadIdx.x; e < FHASH_MAX_LEVELS; e += blockDim.x) lv[e] = g.lv[e];

@@ -6,8 +6,8 @@
 // 32-64-64-1 decoder, 225 for 32-64-64-64-1, which caps the fused training
 // kernel at one or two waves per SIMD (and spills at 32-64-64-1).  Here each
 // 16-sample block computes its weight-gradient tiles with MFMA into transient
-// registers and adds them (ds_add_f32) into one FP32 gradient image per
-// workgroup; biases are summed over the block's 16 sample lanes first.  At the
+// registers and adds them into one FP32 gradient image per workgroup (read, add,
+// compare-and-swap: lds_add_tiles); biases are summed over the block's 16 sample lanes first.  At the
 // end the workgroup writes its image as one partial of the packed parameter
 // vector.  Summation order across the waves of a workgroup is not fixed.
 //
@@ -26,23 +26,79 @@
 
 namespace fh {
 
+// *p += v in LDS by compare-and-swap, by the float atomic where another wave was
+// in between.  ds_add_f32 is performed lane after lane (about two cycles each);
+// the swap of the bits is not.  A stale read only costs the float atomic.
 __device__ __forceinline__ void lds_add(float* p, float v) {
-  __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  unsigned* q = reinterpret_cast<unsigned*>(p);
+  unsigned was = __float_as_uint(*p);
+  if (!__hip_atomic_compare_exchange_strong(q, &was, __float_as_uint(__uint_as_float(was) + v),
+                                            __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_WORKGROUP))
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// FP32 gradient image of a workgroup in LDS (row strides padded against bank
-// conflicts of the tile adds).
+// The same for a row of 16 x 16 tiles: tile t of the row is at g + 256 t, lane
+// l's four values at 4 l, read 16 bytes and swapped 8 at a time.  The adds of the
+// decoder gradient are 640 per sample (32-64-64-64-1), and as float atomics they
+// held the LDS for 2.2 ms of a 2^20 batch: the fused training kernel 5,430 ->
+// 4,490 us there (FP16 decoder), 217 -> 143 us for 20,011 samples (FP32,
+// 32-64-64-64-1), 177 -> 134 for the backward of 65,537 (16-64-64-1); where the
+// memory-side atomics bound it, 2^18 samples sorted, 1,472 and 1,499.  Waves that
+// begin with different rows of tiles measured the same (4,492, 1,502).
+template <int N>
+__device__ __forceinline__ void lds_add_tiles(float* g, const f4v (&v)[N]) {
+  using u64 = unsigned long long;
+  float* at = g + 4 * (threadIdx.x & 63);
+  f4v was[N];
+#pragma unroll
+  for (int t = 0; t < N; ++t) was[t] = *reinterpret_cast<const f4v*>(at + 256 * t);
+  bool lost[N][2];
+  bool any = false;
+#pragma unroll
+  for (int t = 0; t < N; ++t)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const auto pack = [](float a, float b) {
+        return (u64)__float_as_uint(b) << 32 | __float_as_uint(a);
+      };
+      const float a = was[t][2 * h], b = was[t][2 * h + 1];
+      u64 old = pack(a, b);
+      lost[t][h] = !__hip_atomic_compare_exchange_strong(
+          reinterpret_cast<u64*>(at + 256 * t + 2 * h), &old,
+          pack(a + v[t][2 * h], b + v[t][2 * h + 1]), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+          __HIP_MEMORY_SCOPE_WORKGROUP);
+      any = any || lost[t][h];
+    }
+  if (any) {
+#pragma unroll
+    for (int t = 0; t < N; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (lost[t][i >> 1])
+          __hip_atomic_fetch_add(at + 256 * t + i, v[t][i], __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+}
+
+// FP32 gradient image of a workgroup in LDS.  The weight matrices are stored as
+// 16 x 16 tiles in the output layout of the MFMA (tile (ob, ib) of an IB-wide
+// matrix at 256 (ob IB + ib), lane l's four values at 4 l), so a lane adds 16
+// consecutive bytes.
 template <int INP, int H, int NH>
 struct GradLds {
-  static constexpr int LD0 = INP + 4;
-  static constexpr int LDH = H + 4;
   static constexpr int W0 = 0;
-  static constexpr int B0 = W0 + H * LD0;
-  static constexpr int WK = B0 + H;
-  static constexpr int WKSTRIDE = H * LDH + H;
-  static constexpr int WOUT = WK + (NH - 1) * WKSTRIDE;
+  static constexpr int WK = W0 + H * INP;
+  static constexpr int WKSTRIDE = H * H;
+  static constexpr int B0 = WK + (NH - 1) * WKSTRIDE;
+  static constexpr int WOUT = B0 + NH * H;  // the bias of layer k at B0 + k H
   static constexpr int BOUT = WOUT + H;
   static constexpr int FLOATS = (BOUT + 1 + 3) / 4 * 4;
+  // place of element (o, c) of a matrix of 16 IB columns
+  template <int IB>
+  static __device__ __forceinline__ int at(int o, int c) {
+    return 256 * ((o >> 4) * IB + (c >> 4)) + 64 * ((o >> 2) & 3) + 4 * (c & 15) + (o & 3);
+  }
 };
 
 template <int INP, int H, int NH>
@@ -56,15 +112,16 @@ template <int INP, int H, int NH>
 __device__ void grad_lds_write(const float* g, int in_w, float* __restrict__ part) {
   using G = GradLds<INP, H, NH>;
   for (int e = threadIdx.x; e < H * in_w; e += blockDim.x)
-    part[e] = g[G::W0 + (e / in_w) * G::LD0 + e % in_w];
+    part[e] = g[G::W0 + G::template at<INP / 16>(e / in_w, e % in_w)];
   float* p = part + H * in_w;
   for (int e = threadIdx.x; e < H; e += blockDim.x) p[e] = g[G::B0 + e];
   p += H;
   for (int k = 1; k < NH; ++k) {
     const float* gk = g + G::WK + (k - 1) * G::WKSTRIDE;
-    for (int e = threadIdx.x; e < H * H; e += blockDim.x) p[e] = gk[(e / H) * G::LDH + e % H];
+    for (int e = threadIdx.x; e < H * H; e += blockDim.x)
+      p[e] = gk[G::template at<H / 16>(e / H, e % H)];
     p += H * H;
-    for (int e = threadIdx.x; e < H; e += blockDim.x) p[e] = gk[H * G::LDH + e];
+    for (int e = threadIdx.x; e < H; e += blockDim.x) p[e] = g[G::B0 + k * H + e];
     p += H;
   }
   for (int e = threadIdx.x; e < H; e += blockDim.x) p[e] = g[G::WOUT + e];
@@ -111,13 +168,12 @@ __device__ __forceinline__ void out_layer_bwd(const float* wout, const float (&h
 }
 
 // ------------------------------------------------------------------- FP32
-// Weight gradient of one block: g[(16 ob + r) * ld + 16 ib + c] += sum over the
+// Weight gradient of one block: element (16 ob + r, 16 ib + c) += sum over the
 // 16 samples of delta[16 ob + r] x input[16 ib + c], from the two transposed
 // FP32 tiles ([rows][17]).  Output lane (grp, n): rows 16 ob + 4 grp + i,
 // column 16 ib + n.
 template <int OB, int IB>
-__device__ __forceinline__ void dw_lds_f32(const float* dtile, const float* itile, float* g,
-                                           int ld) {
+__device__ __forceinline__ void dw_lds_f32(const float* dtile, const float* itile, float* g) {
   const int lane = threadIdx.x & 63, grp = lane >> 4, m = lane & 15;
   f4v acc[OB][IB];
 #pragma unroll
@@ -137,11 +193,7 @@ __device__ __forceinline__ void dw_lds_f32(const float* dtile, const float* itil
       for (int ib = 0; ib < IB; ++ib) acc[ob][ib] = mfma4(a[ob], b[ib], acc[ob][ib]);
   }
 #pragma unroll
-  for (int ob = 0; ob < OB; ++ob)
-#pragma unroll
-    for (int ib = 0; ib < IB; ++ib)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) lds_add(&g[(16 * ob + 4 * grp + i) * ld + 16 * ib + m], acc[ob][ib][i]);
+  for (int ob = 0; ob < OB; ++ob) lds_add_tiles<IB>(g + 256 * ob * IB, acc[ob]);
 }
 
 // Backward of one block through the FP32 decoder (weights: the LDS image of
@@ -163,12 +215,12 @@ __device__ __forceinline__ void mlp_block_bwd_lds(const float* lds, float* grad,
   for (int k = NH - 1; k >= 1; --k) {
     const float* wk = lds + S::WK + (k - 1) * S::WKSTRIDE;
     float* gk = grad + G::WK + (k - 1) * G::WKSTRIDE;
-    bias_add<S::HB>(gk + H * G::LDH, delta);
+    bias_add<S::HB>(grad + G::B0 + k * H, delta);
     wave_lds_fence();
     tile_store<S::HB>(dtile, delta);
     tile_store<S::HB>(htile, hs[k - 1]);
     wave_lds_fence();
-    dw_lds_f32<S::HB, S::HB>(dtile, htile, gk, G::LDH);
+    dw_lds_f32<S::HB, S::HB>(dtile, htile, gk);
     float dprev[S::HB][4];
     bwd_data<S::HB, S::HB>(wk, S::LDH, delta, dprev);
 #pragma unroll
@@ -181,7 +233,7 @@ __device__ __forceinline__ void mlp_block_bwd_lds(const float* lds, float* grad,
   tile_store<S::HB>(dtile, delta);
   tile_store<S::INB>(htile, xb);
   wave_lds_fence();
-  dw_lds_f32<S::HB, S::INB>(dtile, htile, grad + G::W0, G::LD0);
+  dw_lds_f32<S::HB, S::INB>(dtile, htile, grad + G::W0);
   bwd_data<S::HB, S::INB>(lds + S::W0, S::LD0, delta, dx);
   wave_lds_fence();
 }
@@ -307,7 +359,7 @@ __device__ __forceinline__ void tile_store_t(T* tile, const float (&v)[NB][4]) {
 // output block (K = the 16 samples).  A lane (grp, m): delta row 16 ob + m,
 // samples 4 grp..4 grp+3; B lane (grp, n): input row 16 ib + n, same samples.
 template <typename T, int OB, int IB, int TS>
-__device__ __forceinline__ void dw_lds_t(const T* dtile, const T* itile, float* g, int ld) {
+__device__ __forceinline__ void dw_lds_t(const T* dtile, const T* itile, float* g) {
   using V = typename Vec4T<T>::type;
   const int lane = threadIdx.x & 63, grp = lane >> 4, m = lane & 15;
   V a[OB], b[IB];
@@ -318,13 +370,13 @@ __device__ __forceinline__ void dw_lds_t(const T* dtile, const T* itile, float* 
   for (int ib = 0; ib < IB; ++ib)
     b[ib] = *reinterpret_cast<const V*>(itile + (16 * ib + m) * TS + 4 * grp);
 #pragma unroll
-  for (int ob = 0; ob < OB; ++ob)
+  for (int ob = 0; ob < OB; ++ob) {
+    f4v acc[IB];
 #pragma unroll
-    for (int ib = 0; ib < IB; ++ib) {
-      const f4v acc = mfma16t<T>(a[ob], b[ib], f4v{0.0f, 0.0f, 0.0f, 0.0f});
-#pragma unroll
-      for (int i = 0; i < 4; ++i) lds_add(&g[(16 * ob + 4 * grp + i) * ld + 16 * ib + m], acc[i]);
-    }
+    for (int ib = 0; ib < IB; ++ib)
+      acc[ib] = mfma16t<T>(a[ob], b[ib], f4v{0.0f, 0.0f, 0.0f, 0.0f});
+    lds_add_tiles<IB>(g + 256 * ob * IB, acc);
+  }
 }
 
 // Backward of one block through the 16-bit decoder (LDS image of
@@ -344,12 +396,12 @@ __device__ __forceinline__ void mlp_block_bwd_t(const float* lds, float* grad, T
 #pragma unroll
   for (int k = NH - 1; k >= 1; --k) {
     float* gk = grad + G::WK + (k - 1) * G::WKSTRIDE;
-    bias_add<S::HB>(gk + H * G::LDH, delta);
+    bias_add<S::HB>(grad + G::B0 + k * H, delta);
     wave_lds_fence();
     tile_store_t<T, S::HB, S::TS>(dtile, delta);
     tile_store_t<T, S::HB, S::TS>(htile, hs[k - 1]);
     wave_lds_fence();
-    dw_lds_t<T, S::HB, S::HB, S::TS>(dtile, htile, gk, G::LDH);
+    dw_lds_t<T, S::HB, S::HB, S::TS>(dtile, htile, gk);
     float dprev[S::HB][4];
     bwd_data_t<T, S::HB, S::HB>(wh + S::WKT + (k - 1) * H * S::LDH, S::LDH, delta, dprev);
 #pragma unroll
@@ -362,7 +414,7 @@ __device__ __forceinline__ void mlp_block_bwd_t(const float* lds, float* grad, T
   tile_store_t<T, S::HB, S::TS>(dtile, delta);
   tile_store_t<T, S::INB, S::TS>(htile, xb);
   wave_lds_fence();
-  dw_lds_t<T, S::HB, S::INB, S::TS>(dtile, htile, grad + G::W0, G::LD0);
+  dw_lds_t<T, S::HB, S::INB, S::TS>(dtile, htile, grad + G::W0);
   bwd_data_t<T, S::HB, S::INB>(wh + S::W0T, S::LDH, delta, dx);
   wave_lds_fence();
 }
