@@ -1064,11 +1064,11 @@ def _to_psnr(model, step, k_done, t_first, ppos, ptgt, target, eval_every, max_s
 
 def coarse_levels(res, n):
     """Levels of two features that FHASH_COARSE_LDS sends through the LDS
-    scatter: from the coarsest on, those with at most two cells per sample of
+    scatter: from the coarsest on, those with at most four cells per sample of
     the batch (smaller batches: or at most 8000 and n vertices)."""
     lc = 0
     for r in res:
-        if ((r[0] - 1) * (r[1] - 1) * (r[2] - 1) * (r[3] - 1) > 2 * n
+        if ((r[0] - 1) * (r[1] - 1) * (r[2] - 1) * (r[3] - 1) > 4 * n
                 and r[0] * r[1] * r[2] * r[3] > min(8000, n)):
             break
         lc += 1
@@ -1335,7 +1335,7 @@ def headline_bench(args):
     alg = (3092 if reads16 else 4116) * B
     comp = mx["compulsory"]["bytes"]
     # with FHASH_COARSE_LDS the fused kernel issues the requests of the levels
-    # with more than two cells per sample only; the coarse levels' requests are
+    # with more than four cells per sample only; the coarse levels' requests are
     # replaced by one per touched vertex row segment of a chunk's LDS box
     # (the library takes the LDS path on row-ordered indexes only)
     lc = coarse_levels(cfg.res, B) if args.coarse_lds and args.layout == "rows" else 0

@@ -278,7 +278,7 @@ int fhash_fused_fwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
  * of 16 floats separated by 16-float gaps (gradient value i at
  * d_table[i + 16 floor(i / 16)]; the gradient array of the optimiser layout
  * FHASH_MOMENTS_WITH_PARAMS below); the table read is independent of it
- * (table_dt).  FHASH_COARSE_LDS: the levels with at most two cells per
+ * (table_dt).  FHASH_COARSE_LDS: the levels with at most four cells per
  * sample of the batch (one for more than two features; 0 .. lc - 1, coarsest
  * first; row-ordered indexes only, ignored on brick-ordered ones) are not added by the fused kernel: their
  * encoding gradient goes to the workspace, and a second kernel on the same

@@ -166,10 +166,11 @@ static int apply_touch(const fhash_touch* t, int64_t len, fh::GridDev* g) {
 
 // Levels 0 .. lc - 1 whose gradient goes through the LDS scatter (row order
 // only).  FHASH_COARSE_LDS and FHASH_SAMPLES_SORTED: the coarse levels with at
-// most two cells per sample of the batch (one for F > 2, whose boxes are larger),
-// where the chunks of a sorted batch share vertices.  Whole steps with one, two
-// and four cells per sample: FP32 2^18, F = 2, 16 levels 3176, 3127, 3084 us;
-// mixed 2^20 9767, 9781, 9893; F = 1 2632 and 2547; F = 4, 8 levels 2204 and 2280.
+// most four cells per sample of the batch (one for F > 2, whose boxes are larger
+// and more often exceed the LDS image), where the chunks of a sorted batch share
+// vertices.  Whole steps with two, four and eight cells per sample: FP32 2^18,
+// F = 2, 16 levels 3162, 3133, 3148 us; 60,000 samples 1247, 1234, 1241; mixed
+// 2^20 8786, 8678, 8620; F = 4, 8 levels with one and two 2074 and 2122.
 // In any batch: levels so small that their whole vertex box
 // fits the LDS image and that every vertex takes 16 or more corners' adds
 // (n >= vertices): atomics into one 64-byte line are performed one after
@@ -181,7 +182,7 @@ static int apply_touch(const fhash_touch* t, int64_t len, fh::GridDev* g) {
 static int coarse_levels(const fhash_index* idx, int64_t n, uint32_t flags) {
   if (idx->grid.layout != FHASH_LAYOUT_ROWS) return 0;
   const bool shared = (flags & (FHASH_COARSE_LDS | FHASH_SAMPLES_SORTED)) != 0;
-  const double most = (idx->grid.n_features <= 2 ? 2.0 : 1.0) * (double)n;
+  const double most = (idx->grid.n_features <= 2 ? 4.0 : 1.0) * (double)n;
   int lc = 0;
   for (int l = 0; l < idx->grid.n_levels; ++l) {
     const int32_t* r = idx->grid.res[l];
