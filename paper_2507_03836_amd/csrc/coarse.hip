@@ -29,7 +29,7 @@ constexpr int kWhole = 4096;  // floats of a level that can be the box itself
 constexpr int kThreads = 1024;  // 16 waves: the loops below wait on L2 latency
 constexpr int kChunk = 2048;    // samples per workgroup, at most
 constexpr int kChunkMin = 256;  // and at least: a box is cleared and added per chunk
-constexpr int kUnroll = 4;      // independent loads in flight per thread
+constexpr int kUnroll = 2;      // independent loads in flight per thread (4 take 4 more registers)
 constexpr int kParts = 4;       // a chunk whose box does not fit is retried in 4 parts
 constexpr int kTries = 3;       // compare-and-swaps before the float atomic
 constexpr int kCap = kCoarseFloats;  // floats of the LDS image (with the reduction slots, under 64 KiB)
@@ -125,8 +125,11 @@ __device__ __forceinline__ void lds_add(float* at, const float* run) {
   }
 }
 
+// Two workgroups (32 waves) to a CU take 64 registers a thread: 2^20 samples, nine
+// levels, F = 2: 801 us with 68 registers and one workgroup, 670 with two; 2^18:
+// 214 and 188.  For F = 4 the spills take it back (123 and 125 us).
 template <int F>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, F <= 2 ? 8 : 4)
     coarse_scatter_kernel(GridDev g, const float4* __restrict__ pos, int64_t n,
                           const float* __restrict__ grad, int64_t level_step,
                           int64_t sample_step, int chunk, float* __restrict__ d_table) {
