@@ -42,6 +42,7 @@ struct FusedArgs {
   float* part;     // per-workgroup parameter-gradient partials
   double* loss_sum;
   int64_t P;
+  int waves;   // of a workgroup that take blocks (FusedLaunch)
   float coef;  // dL/dy = coef * (y - target)
   int in_w;    // L * F
 };
@@ -165,8 +166,8 @@ template <int MODE, int F, typename T, int INP, int H, int NH, typename D, bool 
 __global__ void __launch_bounds__(64 * waves_per_block(MODE))
     __attribute__((amdgpu_waves_per_eu(is_forward(MODE) ? 1 : 2)))
     fused_kernel(GridDev g, FusedArgs A) {
-  constexpr int kWaves = waves_per_block(MODE);  // of LDS; blockDim.x / 64 of them run
-  const int nw = blockDim.x >> 6;
+  constexpr int kWaves = waves_per_block(MODE);  // every workgroup's, nw of them take blocks
+  const int nw = A.waves;
   constexpr bool FWD = is_forward(MODE);
   if constexpr (FWD) {
     if (A.n_dev != nullptr) {
@@ -186,19 +187,12 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
                            : train_wave_scratch_t<INP, H, NH>();
   __shared__ __attribute__((aligned(16))) float lds[WFL + GFL + kWaves * WS + 1];
   __shared__ LevelDev lv[FHASH_MAX_LEVELS];
-  auto stage = [&](auto threads) {
-    constexpr int N = decltype(threads)::value;
-    if constexpr (MODE == MODE_FWD16)
-      load_weights_lds_h<INP, H, NH, D, N>(lds, A.params, A.in_w);
-    else if constexpr (D32)
-      load_weights_lds<INP, H, NH, N>(lds, A.params, A.in_w);
-    else
-      load_weights_lds_t<INP, H, NH, D, N>(lds, A.params, A.in_w);
-  };
-  if (nw == kWaves)
-    stage(std::integral_constant<int, 64 * kWaves>());
+  if constexpr (MODE == MODE_FWD16)
+    load_weights_lds_h<INP, H, NH, D, 64 * kWaves>(lds, A.params, A.in_w);
+  else if constexpr (D32)
+    load_weights_lds<INP, H, NH, 64 * kWaves>(lds, A.params, A.in_w);
   else
-    stage(std::integral_constant<int, 0>());
+    load_weights_lds_t<INP, H, NH, D, 64 * kWaves>(lds, A.params, A.in_w);
   static_assert(WFL % 4 == 0, "the gradient image is read 16 bytes at a time");
   float* grad = lds + WFL;
   if constexpr (!FWD) grad_lds_zero<INP, H, NH>(grad);
@@ -212,7 +206,7 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
   const int64_t nwav = (int64_t)gridDim.x * nw;
   const int64_t wave = (int64_t)blockIdx.x * nw + wib;
   double loss = 0.0;
-  for (int64_t b = wave; b < nblk; b += nwav) {
+  for (int64_t b = wib < nw ? wave : nblk; b < nblk; b += nwav) {
     // Keep the decoder weights in LDS rather than in registers across blocks:
     // the compiler would otherwise hoist every layer's weight fragments out of
     // this loop (64 registers per 64x64 layer) and cut the waves per SIMD.
@@ -256,7 +250,7 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
     grad_lds_write<INP, H, NH>(grad, A.in_w, A.part + (int64_t)blockIdx.x * A.P);
     if (MODE == MODE_TRAIN && A.loss_sum != nullptr) {
       for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
-      if (lane == 0) unsafeAtomicAdd(A.loss_sum, loss);
+      if (lane == 0 && wib < nw) unsafeAtomicAdd(A.loss_sum, loss);
     }
   }
 }
@@ -268,7 +262,13 @@ __global__ void __launch_bounds__(64 * waves_per_block(MODE))
 // workgroups first, a CU each: the lookups of 16 samples are about 4,000 line
 // requests, one per cycle and CU, so eight waves on one CU and 248 CUs idle
 // waited for each other.  1000 points, 8 waves on 8 CUs / a wave on each of 63:
-// 33.1 / 23.2 us, 19.1 with the weights staged in one latency.
+// 33.1 / 23.2 us, 19.1 with the weights staged in one latency.  Every workgroup is
+// launched with eight waves all the same, and those without a block only help to
+// stage: a workgroup of one wave held the whole decoder in its registers on the
+// way to LDS, which set the kernel's register count for every batch (forward of
+// 32-64-64-64-1: 234 registers, now 100, two workgroups to a CU).  1000 points
+// 19.1 -> 12.8 us, the decodes of four 512 x 512 renders and three point queries
+// 9.38 -> 7.22 ms, the training kernel of 20,011 samples 143 -> 132 us.
 struct FusedLaunch {
   int64_t blocks;
   int waves;
@@ -293,7 +293,8 @@ constexpr bool brick_shape() {
 template <int MODE, int F, typename T, int INP, int H, int NH, typename D>
 hipError_t fused_t(const GridDev& g, FusedArgs A, float* d_params, hipStream_t st) {
   const FusedLaunch fl = fused_launch(A.n, MODE);
-  const dim3 grid((unsigned)fl.blocks), block(64 * fl.waves);
+  A.waves = fl.waves;
+  const dim3 grid((unsigned)fl.blocks), block(64 * waves_per_block(MODE));
   if (g.lv[0].brick) {
     if constexpr (brick_shape<F, INP, H, NH>())
       hipLaunchKernelGGL((fused_kernel<MODE, F, T, INP, H, NH, D, true>), grid, block, 0, st, g, A);

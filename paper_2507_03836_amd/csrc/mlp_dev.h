@@ -44,21 +44,21 @@ struct MlpShape {
   static constexpr int SCRATCH = 2 * TILE;
 };
 
-// A thread's share of N values, elements threadIdx.x + k T of a workgroup of T =
-// THREADS threads (or of any whole waves, THREADS = 0).  Loading every part of
+// A thread's share of N values, elements threadIdx.x + k THREADS of a workgroup of
+// THREADS threads.  Loading every part of
 // the decoder before the first store keeps one latency between a workgroup and
 // its weights; with a loop over blockDim.x every load was waited for, 12 to 40
 // latencies in a chain (mlp_fwd_kernel<64, 64, 2> on 100,003 samples 54 us, so
 // and with float4 inputs 28).
 template <int N, int THREADS>
 struct Staged {
-  static constexpr int K = (N + (THREADS > 0 ? THREADS : 64) - 1) / (THREADS > 0 ? THREADS : 64);
+  static constexpr int K = (N + THREADS - 1) / THREADS;
   float v[K];
   static __device__ __forceinline__ int at(int k) {
-    return k * (THREADS > 0 ? THREADS : (int)blockDim.x) + (int)threadIdx.x;
+    return k * THREADS + (int)threadIdx.x;
   }
   static __device__ __forceinline__ bool has(int k) {
-    return (THREADS > 0 && N % THREADS == 0) || at(k) < N;
+    return N % THREADS == 0 || at(k) < N;
   }
   template <typename Fn>
   __device__ __forceinline__ void load(Fn fn) {
