@@ -90,14 +90,17 @@ inline void make_grid_dev(const fhash_index* idx, GridDev* g) {
 #ifdef __HIPCC__
 // Cell location along one dimension (Sec. 3.2.4 steps 1-2).  Clamp to [0,1]
 // (NaN -> 0 via IEEE maxNum), one FP32 multiply, floor, clamp to R-2, exact
-// fraction.  __fmul_rn / __fsub_rn keep the compiler from contracting.
+// fraction of the rounded product.  __fmul_rn and __fsub_rn alone do not keep the
+// compiler from contracting the two where the product's other use ends up in
+// another block; the pragma does.
 __device__ __forceinline__ void locate(float p, int R, float s, int& cell, float& frac) {
+#pragma clang fp contract(off)
   p = fminf(fmaxf(p, 0.0f), 1.0f);
-  float u = __fmul_rn(p, s);
+  const float u = p * s;
   int i = (int)floorf(u);
   i = min(i, R - 2);
   cell = i;
-  frac = __fsub_rn(u, (float)i);
+  frac = u - (float)i;
 }
 
 // Row of vertex (x, y, z, t) in a hashed level (see fhash_hash_index).
