@@ -279,7 +279,7 @@ int fhash_fused_fwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
  * d_table[i + 16 floor(i / 16)]; the gradient array of the optimiser layout
  * FHASH_MOMENTS_WITH_PARAMS below); the table read is independent of it
  * (table_dt).  FHASH_COARSE_LDS: the levels with at most four cells per
- * sample of the batch (one for more than two features; 0 .. lc - 1, coarsest
+ * sample of the batch (one for more than two features or a hashed index; 0 .. lc - 1, coarsest
  * first; row-ordered indexes only, ignored on brick-ordered ones) are not added by the fused kernel: their
  * encoding gradient goes to the workspace, and a second kernel on the same
  * stream sums it per chunk of up to 2048 consecutive samples into an LDS image of
@@ -289,7 +289,7 @@ int fhash_fused_fwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
  * Sorted batches give compact boxes; the results are the same up to FP32
  * summation order.  The workspace then grows by lc x n x F floats (the size
  * query includes it).  Without either flag the coarsest levels of at most n
- * vertices and 16000 floats take the same path.  Other bits: FHASH_EINVAL.  touch: NULL, or segment
+ * vertices and 16000 floats take the same path (not on a hashed index).  Other bits: FHASH_EINVAL.  touch: NULL, or segment
  * flags of d_table to set, by logical float index (see fhash_touch). */
 #define FHASH_SAMPLES_SORTED 1u
 #define FHASH_GRAD_PAIRED 2u

@@ -178,17 +178,20 @@ static int apply_touch(const fhash_touch* t, int64_t len, fh::GridDev* g) {
 // 65,537 points on a fold-2 dense box (F = 1, levels of 16 to 2,760 vertices and
 // larger) for 7.8 ms; through LDS the same backward takes 0.18 + 0.05 ms.  At
 // the edge (4,096 samples, 1,536 vertices, F = 2) the step takes 77 us with the
-// level in LDS, 102 us with it and a level of 128 vertices in the kernel.
+// level in LDS, 102 us with it and a level of 128 vertices in the kernel.  A hashed
+// index, whose box vertices fall on unrelated rows so that the flush shares no
+// requests, takes the levels of at most one cell per sample, and with a flag only.
 static int coarse_levels(const fhash_index* idx, int64_t n, uint32_t flags) {
   if (idx->grid.layout != FHASH_LAYOUT_ROWS) return 0;
   const bool shared = (flags & (FHASH_COARSE_LDS | FHASH_SAMPLES_SORTED)) != 0;
-  const double most = (idx->grid.n_features <= 2 ? 4.0 : 1.0) * (double)n;
+  const double most = (idx->grid.n_features <= 2 && idx->hash_bits == 0 ? 4.0 : 1.0) * (double)n;
   int lc = 0;
   for (int l = 0; l < idx->grid.n_levels; ++l) {
     const int32_t* r = idx->grid.res[l];
     const double cells = (double)(r[0] - 1) * (r[1] - 1) * (r[2] - 1) * (r[3] - 1);
     const double verts = (double)r[0] * r[1] * r[2] * r[3];
-    const bool small = verts * idx->grid.n_features <= fh::kCoarseFloats && verts <= (double)n;
+    const bool small = idx->hash_bits == 0 && verts <= (double)n &&
+                       verts * idx->grid.n_features <= fh::kCoarseFloats;
     if (!small && !(shared && cells <= most)) break;
     lc = l + 1;
   }
