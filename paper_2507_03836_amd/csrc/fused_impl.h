@@ -20,9 +20,9 @@ namespace fh {
 
 namespace fused_detail {
 
-// Waves per workgroup: at most eight in every mode, fewer (the launch decides,
-// fused_launch) where that spreads a small batch over more CUs.  The forward keeps only the
-// decoder weights in LDS; the backward modes also hold the workgroup's
+// Waves per workgroup: eight in every mode; in a small batch fewer of them take
+// blocks (fused_launch), so that it spreads over more CUs.  The forward keeps only
+// the decoder weights in LDS; the backward modes also hold the workgroup's
 // gradient image and per-wave tiles.  MODE_FWD16: the forward with a 16-bit
 // MFMA decoder (inference).
 enum { MODE_FWD = 0, MODE_BWD = 1, MODE_TRAIN = 2, MODE_FWD16 = 3 };
