@@ -279,9 +279,10 @@ int fhash_fused_fwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
  * d_table[i + 16 floor(i / 16)]; the gradient array of the optimiser layout
  * FHASH_MOMENTS_WITH_PARAMS below); the table read is independent of it
  * (table_dt).  FHASH_COARSE_LDS: the levels with at most four cells per
- * sample of the batch (one for more than two features or a hashed index; 0 .. lc - 1, coarsest
- * first; row-ordered indexes only, ignored on brick-ordered ones) are not added by the fused kernel: their
- * encoding gradient goes to the workspace, and a second kernel on the same
+ * sample of the batch (eight for one feature, one for more than two features or
+ * a hashed index; 0 .. lc - 1, coarsest first; row-ordered indexes only, ignored
+ * on brick-ordered ones) are not added by the fused kernel: their encoding
+ * gradient goes to the workspace, and a second kernel on the same
  * stream sums it per chunk of up to 2048 consecutive samples into an LDS image of
  * the vertex box the chunk touches and adds that box with one atomic per
  * touched vertex and feature (a chunk whose box exceeds 16000 floats is taken
@@ -289,8 +290,9 @@ int fhash_fused_fwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
  * Sorted batches give compact boxes; the results are the same up to FP32
  * summation order.  The workspace then grows by lc x n x F floats (the size
  * query includes it).  Without either flag the coarsest levels of at most n
- * vertices and 16000 floats take the same path (not on a hashed index).  Other bits: FHASH_EINVAL.  touch: NULL, or segment
- * flags of d_table to set, by logical float index (see fhash_touch). */
+ * vertices and 16000 floats take the same path (not on a hashed index).  Other
+ * bits: FHASH_EINVAL.  touch: NULL, or segment flags of d_table to set, by
+ * logical float index (see fhash_touch). */
 #define FHASH_SAMPLES_SORTED 1u
 #define FHASH_GRAD_PAIRED 2u
 #define FHASH_COARSE_LDS 4u

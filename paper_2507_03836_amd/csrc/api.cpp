@@ -166,17 +166,19 @@ static int apply_touch(const fhash_touch* t, int64_t len, fh::GridDev* g) {
 
 // Levels 0 .. lc - 1 whose gradient goes through the LDS scatter (row order
 // only).  FHASH_COARSE_LDS and FHASH_SAMPLES_SORTED: the coarse levels with at
-// most four cells per sample of the batch (one for F > 2, whose boxes are larger
-// and more often exceed the LDS image), where the chunks of a sorted batch share
-// vertices.  Whole steps with two, four and eight cells per sample: FP32 2^18,
-// F = 2, 16 levels 3162, 3133, 3148 us; 60,000 samples 1247, 1234, 1241; mixed
-// 2^20 8786, 8678, 8620; F = 4, 8 levels with one and two 2074 and 2122.
+// most four cells per sample of the batch (eight for F = 1; one for F > 2, whose
+// boxes are larger and more often exceed the LDS image), where the chunks of a
+// sorted batch share vertices.  Whole steps with two, four and eight cells per
+// sample: FP32 2^18, F = 2, 16 levels 3162, 3133, 3148 us; 60,000 samples 1247,
+// 1234, 1241; mixed 2^20 8786, 8678, 8620; with two workgroups of the scatter per
+// CU, four and eight: 3091 and 3112; 1236 and 1239; 8587 and 8485; 300,000 samples
+// 3479 and 3494; F = 1 2453 and 2410.  F = 4, 8 levels, one and two 2074 and 2122.
 // In any batch: levels so small that their whole vertex box
 // fits the LDS image and that every vertex takes 16 or more corners' adds
 // (n >= vertices): atomics into one 64-byte line are performed one after
 // another, about 10 ns each, so levels of a few vertices held the backward of
 // 65,537 points on a fold-2 dense box (F = 1, levels of 16 to 2,760 vertices and
-// larger) for 7.8 ms; through LDS the same backward takes 0.18 + 0.05 ms.  At
+// larger) for 7.8 ms; through LDS the same backward takes 0.13 + 0.025 ms.  At
 // the edge (4,096 samples, 1,536 vertices, F = 2) the step takes 77 us with the
 // level in LDS, 102 us with it and a level of 128 vertices in the kernel.  A hashed
 // index, whose box vertices fall on unrelated rows so that the flush shares no
@@ -184,7 +186,8 @@ static int apply_touch(const fhash_touch* t, int64_t len, fh::GridDev* g) {
 static int coarse_levels(const fhash_index* idx, int64_t n, uint32_t flags) {
   if (idx->grid.layout != FHASH_LAYOUT_ROWS) return 0;
   const bool shared = (flags & (FHASH_COARSE_LDS | FHASH_SAMPLES_SORTED)) != 0;
-  const double most = (idx->grid.n_features <= 2 && idx->hash_bits == 0 ? 4.0 : 1.0) * (double)n;
+  const double most =
+      (idx->grid.n_features <= 2 && idx->hash_bits == 0 ? 8 / idx->grid.n_features : 1) * (double)n;
   int lc = 0;
   for (int l = 0; l < idx->grid.n_levels; ++l) {
     const int32_t* r = idx->grid.res[l];
