@@ -28,10 +28,13 @@ namespace fh {
 
 // *p += v in LDS by compare-and-swap, by the float atomic where another wave was
 // in between.  ds_add_f32 is performed lane after lane (about two cycles each);
-// the swap of the bits is not.  A stale read only costs the float atomic.
+// the swap of the bits is not.  The read is a relaxed atomic: other waves swap the
+// same word, and one value has to feed both the comparand and the sum (an ordinary
+// load may be repeated by the compiler, and the swap then succeed on a sum of an
+// older value).  A stale read only costs the float atomic.
 __device__ __forceinline__ void lds_add(float* p, float v) {
   unsigned* q = reinterpret_cast<unsigned*>(p);
-  unsigned was = __float_as_uint(*p);
+  unsigned was = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   if (!__hip_atomic_compare_exchange_strong(q, &was, __float_as_uint(__uint_as_float(was) + v),
                                             __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                             __HIP_MEMORY_SCOPE_WORKGROUP))
@@ -39,7 +42,7 @@ __device__ __forceinline__ void lds_add(float* p, float v) {
 }
 
 // The same for a row of 16 x 16 tiles: tile t of the row is at g + 256 t, lane
-// l's four values at 4 l, read 16 bytes and swapped 8 at a time.  The adds of the
+// l's four values at 4 l, read and swapped 8 bytes at a time.  The adds of the
 // decoder gradient are 640 per sample (32-64-64-64-1), and as float atomics they
 // held the LDS for 2.2 ms of a 2^20 batch: the fused training kernel 5,430 ->
 // 4,490 us there (FP16 decoder), 217 -> 143 us for 20,011 samples (FP32,
@@ -50,23 +53,24 @@ template <int N>
 __device__ __forceinline__ void lds_add_tiles(float* g, const f4v (&v)[N]) {
   using u64 = unsigned long long;
   float* at = g + 4 * (threadIdx.x & 63);
-  f4v was[N];
+  u64 was[N][2];
 #pragma unroll
-  for (int t = 0; t < N; ++t) was[t] = *reinterpret_cast<const f4v*>(at + 256 * t);
+  for (int t = 0; t < N; ++t)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      was[t][h] = __hip_atomic_load(reinterpret_cast<u64*>(at + 256 * t + 2 * h),
+                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   bool lost[N][2];
   bool any = false;
 #pragma unroll
   for (int t = 0; t < N; ++t)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const auto pack = [](float a, float b) {
-        return (u64)__float_as_uint(b) << 32 | __float_as_uint(a);
-      };
-      const float a = was[t][2 * h], b = was[t][2 * h + 1];
-      u64 old = pack(a, b);
+      const float a = __uint_as_float((unsigned)was[t][h]) + v[t][2 * h];
+      const float b = __uint_as_float((unsigned)(was[t][h] >> 32)) + v[t][2 * h + 1];
       lost[t][h] = !__hip_atomic_compare_exchange_strong(
-          reinterpret_cast<u64*>(at + 256 * t + 2 * h), &old,
-          pack(a + v[t][2 * h], b + v[t][2 * h + 1]), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+          reinterpret_cast<u64*>(at + 256 * t + 2 * h), &was[t][h],
+          (u64)__float_as_uint(b) << 32 | __float_as_uint(a), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
           __HIP_MEMORY_SCOPE_WORKGROUP);
       any = any || lost[t][h];
     }
