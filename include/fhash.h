@@ -272,8 +272,7 @@ int fhash_fused_fwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
                     const void* shadow, float* y, void* stream);
 /* flags: FHASH_SAMPLES_SORTED declares that the batch is ordered by
  * fhash_sort_samples: the coarse levels are then summed as under
- * FHASH_COARSE_LDS below (not by fhash_fused_train_static, which has no
- * workspace for it).  Results are the same up to FP32 summation order.
+ * FHASH_COARSE_LDS below.  Results are the same up to FP32 summation order.
  * FHASH_GRAD_PAIRED: d_table is stored in runs
  * of 16 floats separated by 16-float gaps (gradient value i at
  * d_table[i + 16 floor(i / 16)]; the gradient array of the optimiser layout
@@ -312,15 +311,17 @@ int fhash_fused_train(const fhash_index* idx, const fhash_mlp_desc* mlp, const f
  * hipMalloc): fhash_fused_train with no workspace argument.  The decoder-
  * gradient partials go to a scratch array owned by the library, one copy per
  * GPU (FHASH_STATIC_SCRATCH_BYTES = 10,813,440 bytes, held until the process
- * ends); its device address is resolved on the first call on each device, and
- * the call allocates nothing.  Every partial the reduction reads is written by
+ * ends), the coarse levels' encoding gradient to another (16 MiB; batches it
+ * does not hold, more than 131,072 samples at the least, are taken in pieces);
+ * their device addresses are resolved on the first call on each device, and
+ * the call allocates nothing.  Everything that is read from them is written by
  * the same call, so nothing has to start at zero.  All calls on one GPU share
- * the array: calls that overlap on one GPU (different streams, or threads
- * without ordering) race and give wrong d_params.  Otherwise the arguments,
- * results and errors are those of fhash_fused_train; FHASH_ENOMEM if the
- * partials of a launch would exceed the array (never for the decoders the
- * fused path is built for); FHASH_EINVAL for FHASH_COARSE_LDS, whose encoding
- * gradient needs a workspace. */
+ * the arrays: calls that overlap on one GPU (different streams, or threads
+ * without ordering) race and give wrong d_params and d_table.  Otherwise the
+ * arguments, results and errors are those of fhash_fused_train; FHASH_ENOMEM if
+ * the partials of a launch would exceed the array (never for the decoders the
+ * fused path is built for); FHASH_EINVAL for FHASH_COARSE_LDS (FHASH_SAMPLES_SORTED
+ * takes the same path). */
 #define FHASH_STATIC_SCRATCH_BYTES 10813440
 int fhash_fused_train_static(const fhash_index* idx, const fhash_mlp_desc* mlp,
                              const float* pos, const float* target, int64_t n, const void* table,

@@ -496,6 +496,11 @@ int fhash_fused_bwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
                     "fhash_fused_bwd");
 }
 
+// dL/dy = coef * (y - target) of the mean squared error over n samples.
+static float mse_coef(float loss_scale, int64_t n) {
+  return (float)(2.0 * (double)loss_scale / (double)n);
+}
+
 int fhash_fused_train(const fhash_index* idx, const fhash_mlp_desc* mlp, const float* pos,
                       const float* target, int64_t n, const void* table, fhash_dtype table_dt,
                       const float* params, const void* shadow, float loss_scale, float* d_table,
@@ -521,8 +526,8 @@ int fhash_fused_train(const fhash_index* idx, const fhash_mlp_desc* mlp, const f
   if ((rc = apply_touch(touch, total_rows(idx) * idx->grid.n_features, &g))) return rc;
   const fhash_dtype tdt = table_view(table_dt, &g);
   return hip_status(fh::launch_fused_train(g, H, NH, mlp->compute_dt, pos, target, n, table,
-                                           tdt, params, loss_scale, d_table, d_params, loss_sum,
-                                           ws, P, S(stream)),
+                                           tdt, params, mse_coef(loss_scale, n), d_table,
+                                           d_params, loss_sum, ws, P, S(stream)),
                     "fhash_fused_train");
 }
 
@@ -547,17 +552,34 @@ int fhash_fused_train_static(const fhash_index* idx, const fhash_mlp_desc* mlp,
     return fail(FHASH_ENOMEM, "decoder-gradient partials need %zu bytes, the static scratch "
                 "holds %zu", need, fh::static_scratch_bytes());
   void* ws = nullptr;
-  hipError_t e = fh::static_scratch(&ws);
+  float* dxc = nullptr;
+  hipError_t e = fh::static_scratch(&ws, &dxc);
   if (e != hipSuccess) return hip_status(e, "fhash_fused_train_static scratch");
   fh::GridDev g;
   fh::make_grid_dev(idx, &g);
   if ((rc = apply_bwd_flags(flags, &g))) return rc;
   if ((rc = apply_touch(touch, total_rows(idx) * idx->grid.n_features, &g))) return rc;
   const fhash_dtype tdt = table_view(table_dt, &g);
-  return hip_status(fh::launch_fused_train(g, H, NH, mlp->compute_dt, pos, target, n, table,
-                                           tdt, params, loss_scale, d_table, d_params,
-                                           loss_sum, ws, P, S(stream)),
-                    "fhash_fused_train_static");
+  // The coarse levels go through the LDS scatter as in the workspace call, in
+  // pieces of the batch whose encoding gradient the scratch holds (131,072
+  // samples or more).  Added by the fused kernel, levels of a few vertices queue
+  // their atomics on the same lines: 65,537 samples, F = 1, fold-2 dense box,
+  // 8,230 us in draw order and 8,890 us declared sorted, so 182 and 159; 2^18 and
+  // 2^20 sorted samples, F = 2, 16 levels 2,097 and 8,483, so 1,475 and 5,038 (five
+  // pieces; 4,637 in the workspace call).
+  g.coarse = coarse_levels(idx, n, flags);
+  g.dxc = dxc;
+  const int64_t fit =
+      g.coarse > 0 ? fh::kStaticCoarseFloats / (g.coarse * idx->grid.n_features) / 16 * 16 : n;
+  for (int64_t s = 0; s < n; s += fit) {
+    const int64_t m = std::min(fit, n - s);
+    g.nsamp = m;
+    e = fh::launch_fused_train(g, H, NH, mlp->compute_dt, pos + 4 * s, target + s, m, table, tdt,
+                               params, mse_coef(loss_scale, n), d_table, d_params, loss_sum, ws,
+                               P, S(stream));
+    if (e != hipSuccess) break;
+  }
+  return hip_status(e, "fhash_fused_train_static");
 }
 
 // Where the optimiser layout ties the arrays together (fhash_adam_desc).

@@ -53,20 +53,23 @@ hipError_t launch_fused_bwd16(const GridDev& g, int H, int NH, fhash_dtype ddt, 
                               int64_t n, const void* table, fhash_dtype tdt, const float* params,
                               const float* dy, float* d_table, float* d_params, void* ws,
                               int64_t P, hipStream_t st);
+// coef: dL/dy = coef * (y - target)
 hipError_t launch_fused_train(const GridDev& g, int H, int NH, fhash_dtype ddt, const float* pos,
                               const float* target, int64_t n, const void* table, fhash_dtype tdt,
-                              const float* params, float loss_scale, float* d_table,
+                              const float* params, float coef, float* d_table,
                               float* d_params, double* loss_sum, void* ws, int64_t P,
                               hipStream_t st);
 hipError_t launch_fused_train16(const GridDev& g, int H, int NH, fhash_dtype ddt,
                                 const float* pos, const float* target, int64_t n,
                                 const void* table, fhash_dtype tdt, const float* params,
-                                float loss_scale, float* d_table, float* d_params,
+                                float coef, float* d_table, float* d_params,
                                 double* loss_sum, void* ws, int64_t P, hipStream_t st);
 
 // static_ws.hip: library-owned scratch for the entry points that allocate nothing
 size_t static_scratch_bytes();
-hipError_t static_scratch(void** ptr);
+// coarse: kStaticCoarseFloats floats for the coarse levels' encoding gradient
+constexpr int64_t kStaticCoarseFloats = (int64_t)1 << 22;
+hipError_t static_scratch(void** ptr, float** coarse);
 
 // optim.hip
 // Adam over the parameters [first, first + n) of a vector: p, g, m, v and
