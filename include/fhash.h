@@ -288,7 +288,8 @@ int fhash_fused_fwd(const fhash_index* idx, const fhash_mlp_desc* mlp, const flo
  * in 4 parts, and a part that still exceeds it adds its samples directly).
  * Sorted batches give compact boxes; the results are the same up to FP32
  * summation order.  The workspace then grows by lc x n x F floats (the size
- * query includes it).  Without either flag the coarsest levels of at most n
+ * query includes it; it never falls as n grows, so that a workspace sized for
+ * the largest batch holds every smaller one).  Without either flag the coarsest levels of at most n
  * vertices and 16000 floats take the same path (not on a hashed index).  Other
  * bits: FHASH_EINVAL.  touch: NULL, or segment flags of d_table to set, by
  * logical float index (see fhash_touch). */

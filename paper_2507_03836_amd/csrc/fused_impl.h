@@ -280,7 +280,15 @@ inline FusedLaunch fused_launch(int64_t n, int mode) {
   const int64_t waves = each < most ? each : most;
   return {(w + waves - 1) / waves, (int)waves};
 }
-inline int64_t fused_blocks(int64_t n, int mode) { return fused_launch(n, mode).blocks; }
+
+// The most partials that a backward launch of n samples or fewer writes: what a
+// workspace is sized for.  The launch's own count falls wherever another wave
+// joins each workgroup (256 at 4,096 samples, 129 at 4,097), and a workspace that
+// holds a batch has to hold every smaller one.
+inline int64_t fused_most_partials(int64_t n) {
+  const int64_t nblk = n > 0 ? (n + 15) / 16 : 1;
+  return nblk < 256 ? nblk : 256;
+}
 
 // The brick slot order is built for the production decoder shapes only
 // (32 inputs, hidden width 64, 2 or 3 hidden layers, F = 2 or 4); the host

@@ -37,7 +37,6 @@ hipError_t launch_mlp_bwd(int in_w, int H, int NH, const float* params, const fl
 // forward for two features per level only).
 bool fused_supported(int F, int in_w, int H, int NH);
 size_t fused_ws_bytes(int64_t n, int64_t P);
-int64_t fused_partials(int64_t n);
 // n_dev: NULL, or the device's own count of at most n samples
 hipError_t launch_fused_fwd(const GridDev& g, int H, int NH, const float* pos, int64_t n,
                             const void* table, fhash_dtype tdt, const float* params, float* y,
