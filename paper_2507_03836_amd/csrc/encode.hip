@@ -130,6 +130,10 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// Samples of one launch with `per` threads to a sample.  A launch holds fewer than
+// 2^32 threads (2^28 samples of 16 levels have as many); larger batches go in pieces.
+inline int64_t launch_piece(int per) { return ((int64_t)1 << 31) / per; }
+
 template <int F, typename T>
 void launch_fwd_tt(const GridDev& g, const float* pos, int64_t n, const T* table, float* enc,
                    hipStream_t st) {
@@ -146,25 +150,39 @@ void launch_fwd_tt(const GridDev& g, const float* pos, int64_t n, const T* table
 template <int F>
 hipError_t launch_fwd_t(const GridDev& g, const float* pos, int64_t n, const void* table,
                         fhash_dtype dt, float* enc, hipStream_t st) {
-  if (dt == FHASH_F32)
-    launch_fwd_tt<F>(g, pos, n, reinterpret_cast<const float*>(table), enc, st);
-  else
-    launch_fwd_tt<F>(g, pos, n, reinterpret_cast<const __half*>(table), enc, st);
-  return hipGetLastError();
+  const int64_t piece = launch_piece(g.L);
+  for (int64_t s = 0; s < n; s += piece) {
+    const int64_t m = n - s < piece ? n - s : piece;
+    float* e = enc + s * g.L * F;
+    if (dt == FHASH_F32)
+      launch_fwd_tt<F>(g, pos + 4 * s, m, reinterpret_cast<const float*>(table), e, st);
+    else
+      launch_fwd_tt<F>(g, pos + 4 * s, m, reinterpret_cast<const __half*>(table), e, st);
+    if (const hipError_t err = hipGetLastError()) return err;
+  }
+  return hipSuccess;
 }
 
 template <int F>
 hipError_t launch_bwd_t(const GridDev& g, const float* pos, int64_t n, const float* d_enc,
                         float* d_table, hipStream_t st) {
-  const float4* p = reinterpret_cast<const float4*>(pos);
-  if (g.lv[0].brick)
-    hipLaunchKernelGGL((encode_bwd_kernel<F, true>), dim3((unsigned)((n * 2 * F + 255) / 256)),
-                       dim3(256), 0, st, g, p, n, d_enc, d_table);
-  else
-    hipLaunchKernelGGL((encode_bwd_kernel<F, false>), dim3((unsigned)((n * g.L + 255) / 256)),
-                       dim3(256), 0, st, g, p, n, d_enc, d_table);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess || g.coarse == 0) return e;
+  const bool brick = g.lv[0].brick;
+  const int per = brick ? 2 * F : g.L;
+  const int64_t piece = launch_piece(per);
+  for (int64_t s = 0; s < n; s += piece) {
+    const int64_t m = n - s < piece ? n - s : piece;
+    const float4* p = reinterpret_cast<const float4*>(pos) + s;
+    const float* de = d_enc + s * g.L * F;
+    const dim3 grid((unsigned)((m * per + 255) / 256));
+    if (brick)
+      hipLaunchKernelGGL((encode_bwd_kernel<F, true>), grid, dim3(256), 0, st, g, p, m, de,
+                         d_table);
+    else
+      hipLaunchKernelGGL((encode_bwd_kernel<F, false>), grid, dim3(256), 0, st, g, p, m, de,
+                         d_table);
+    if (const hipError_t err = hipGetLastError()) return err;
+  }
+  if (g.coarse == 0) return hipSuccess;
   return launch_coarse_scatter(g, pos, n, d_enc, F, (int64_t)g.L * F, d_table, st);
 }
 
