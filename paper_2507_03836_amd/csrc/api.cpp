@@ -991,7 +991,7 @@ int fhash_render_march_batch(fhash_render_state* const* states, const int32_t* p
   }
   if (need > cap) return fail(FHASH_EINVAL, "sample buffer %lld < out_base + sum pace * alive",
                               (long long)cap);
-  // (the launch pads each request's rays to whole waves: 63 more per request)
+  // (the composite's launch pads each request's rays to whole waves: 63 more)
   if (need + 64 * (int64_t)n > (int64_t)INT32_MAX)
     return fail(FHASH_EINVAL, "out_base + sum pace * alive exceeds 2^31 - 1 - 64 n");
   if (need > out_base && (pos == nullptr || !aligned16(pos)))

@@ -332,18 +332,20 @@ __global__ void __launch_bounds__(kMarchThreads)
 // arm_max), are read here, so the host need not wait for the last iteration to
 // launch the next.  counters: [0], [1] alive rays of the two lists, [2] samples
 // of this iteration, then (64-bit) the samples and iterations so far.  Clears
-// the list length that the composite will append to.
+// the list length that the composite will append to.  first: rays before this
+// launch's.
 template <typename I>
 __global__ void __launch_bounds__(kMarchThreads)
-    march_next_kernel(MarchArgs a, int32_t n_rays, int32_t arm_max, Ray* __restrict__ rays,
-                      const int32_t* __restrict__ alive, float4* __restrict__ out,
-                      int32_t* __restrict__ counters, int cur) {
+    march_next_kernel(MarchArgs a, int64_t first, int32_t n_rays, int32_t arm_max,
+                      Ray* __restrict__ rays, const int32_t* __restrict__ alive,
+                      float4* __restrict__ out, int32_t* __restrict__ counters, int cur) {
   const int32_t n_alive = counters[cur];
   if (blockIdx.x == 0 && threadIdx.x == 0) counters[1 - cur] = 0;
-  if (blockIdx.x * (int64_t)kMarchRays >= n_alive) return;  // uniform
+  const int64_t i0 = first + blockIdx.x * (int64_t)kMarchRays;
+  if (i0 >= n_alive) return;  // uniform
   const int32_t pace = n_rays / n_alive;
   a.pace = pace > arm_max ? arm_max : pace < 1 ? 1 : pace;
-  const int64_t i = blockIdx.x * (int64_t)kMarchRays + threadIdx.x / kSteps;
+  const int64_t i = i0 + threadIdx.x / kSteps;
   const bool act = i < n_alive;
   march_rays<I>(a, rays, act ? alive[i] : 0, act, out, counters + 2, 0);
 }
@@ -384,8 +386,9 @@ __device__ __forceinline__ int wave_request(const Q* q, int32_t n, int64_t i) {
 // counts[0]: sample counter of the launch; counts[1 + r]: samples of request r.
 template <typename I>
 __global__ void __launch_bounds__(kMarchThreads)
-    march_batch_kernel(BatchMarchArgs A, float4* __restrict__ out, int32_t* __restrict__ counts) {
-  const int64_t i0 = blockIdx.x * (int64_t)kMarchRays, i = i0 + threadIdx.x / kSteps;
+    march_batch_kernel(BatchMarchArgs A, int64_t first, float4* __restrict__ out,
+                       int32_t* __restrict__ counts) {
+  const int64_t i0 = first + blockIdx.x * (int64_t)kMarchRays, i = i0 + threadIdx.x / kSteps;
   const int r = wave_request(A.q, A.n, i0);
   const BatchMarchReq& q = A.q[r];
   const int64_t j = i - q.first;
@@ -520,11 +523,25 @@ __global__ void __launch_bounds__(256)
                 &counts[1 + r]);
 }
 
-// The march and composite kernels have no grid-stride loop: at most 2^30 rays,
-// i.e. 2^23 workgroups, well inside the grid limit.
+// The composite kernels have no grid-stride loop: a thread per ray, at most 2^31
+// of the 2^32 threads that a launch has to stay below.
 inline unsigned blocks_exact(int64_t n) {
   const int64_t b = (n + 255) / 256;
   return (unsigned)(b < 1 ? 1 : b);
+}
+
+// The march takes kSteps threads per ray, so 2^29 rays (half of the largest image)
+// are 2^32 threads: fn(first, rays) launches at most 2^28 rays, whole workgroups of
+// them, until all are.
+template <typename Fn>
+hipError_t march_pieces(int64_t rays, Fn fn) {
+  constexpr int64_t kPiece = (int64_t)1 << 28;
+  static_assert(kPiece % kMarchRays == 0 && kPiece * kSteps < ((int64_t)1 << 32), "launch size");
+  for (int64_t first = 0; first < rays; first += kPiece) {
+    fn(first, rays - first < kPiece ? rays - first : kPiece);
+    if (const hipError_t e = hipGetLastError()) return e;
+  }
+  return hipSuccess;
 }
 
 inline unsigned march_blocks(int64_t rays) {
@@ -629,9 +646,10 @@ hipError_t launch_render_march_next(void* ws, int W, int H, const int64_t* dims,
   auto kern = (dims[2] - 1) * (dims[1] - 1) * a.Wc < ((int64_t)1 << 31)
                   ? march_next_kernel<int32_t>
                   : march_next_kernel<int64_t>;
-  hipLaunchKernelGGL(kern, dim3(march_blocks(bound)), dim3(kMarchThreads), 0, st, a, (int32_t)NR,
-                     arm_max, w.rays, w.alive[cur], out, w.counters, cur);
-  return hipGetLastError();
+  return march_pieces(bound, [&](int64_t first, int64_t rays) {
+    hipLaunchKernelGGL(kern, dim3(march_blocks(rays)), dim3(kMarchThreads), 0, st, a, first,
+                       (int32_t)NR, arm_max, w.rays, w.alive[cur], out, w.counters, cur);
+  });
 }
 
 const int32_t* render_sample_count(void* ws, int W, int H) {
@@ -669,16 +687,13 @@ hipError_t launch_render_march(void* ws, int W, int H, const int64_t* dims, floa
   const MarchArgs a = march_args(w, dims, t01, ds, max_steps, pace);
   hipError_t e = hipMemsetAsync(w.counters + 2, 0, 4, st);
   if (e != hipSuccess) return e;
-  if (n_alive > 0) {
-    float4* out = reinterpret_cast<float4*>(pos_out);
-    if ((dims[2] - 1) * (dims[1] - 1) * a.Wc < ((int64_t)1 << 31))
-      hipLaunchKernelGGL(march_kernel<int32_t>, dim3(march_blocks(n_alive)), dim3(kMarchThreads), 0, st, a,
-                         w.rays, w.alive[cur], n_alive, out, w.counters + 2);
-    else
-      hipLaunchKernelGGL(march_kernel<int64_t>, dim3(march_blocks(n_alive)), dim3(kMarchThreads), 0, st, a,
-                         w.rays, w.alive[cur], n_alive, out, w.counters + 2);
-  }
-  e = hipGetLastError();
+  float4* out = reinterpret_cast<float4*>(pos_out);
+  auto kern = (dims[2] - 1) * (dims[1] - 1) * a.Wc < ((int64_t)1 << 31) ? march_kernel<int32_t>
+                                                                        : march_kernel<int64_t>;
+  e = march_pieces(n_alive, [&](int64_t first, int64_t rays) {
+    hipLaunchKernelGGL(kern, dim3(march_blocks(rays)), dim3(kMarchThreads), 0, st, a, w.rays,
+                       w.alive[cur] + first, (int32_t)rays, out, w.counters + 2);
+  });
   if (e != hipSuccess) return e;
   e = hipMemcpyAsync(n_samples_host, w.counters + 2, 4, hipMemcpyDeviceToHost, st);
   if (e != hipSuccess) return e;
@@ -738,16 +753,12 @@ hipError_t launch_render_march_batch(const RenderBatch* b, int32_t n, float ds, 
   }
   hipError_t e = hipMemsetAsync(counts_dev, 0, (size_t)(1 + n) * 4, st);
   if (e != hipSuccess) return e;
-  if (total > 0) {
-    float4* out = reinterpret_cast<float4*>(pos);
-    if (wide)
-      hipLaunchKernelGGL(march_batch_kernel<int64_t>, dim3(march_blocks(total)),
-                         dim3(kMarchThreads), 0, st, A, out, counts_dev);
-    else
-      hipLaunchKernelGGL(march_batch_kernel<int32_t>, dim3(march_blocks(total)),
-                         dim3(kMarchThreads), 0, st, A, out, counts_dev);
-  }
-  e = hipGetLastError();
+  float4* out = reinterpret_cast<float4*>(pos);
+  auto kern = wide ? march_batch_kernel<int64_t> : march_batch_kernel<int32_t>;
+  e = march_pieces(total, [&](int64_t first, int64_t rays) {
+    hipLaunchKernelGGL(kern, dim3(march_blocks(rays)), dim3(kMarchThreads), 0, st, A, first, out,
+                       counts_dev);
+  });
   if (e != hipSuccess) return e;
   e = hipMemcpyAsync(counts_host, counts_dev, (size_t)(1 + n) * 4, hipMemcpyDeviceToHost, st);
   if (e != hipSuccess) return e;
