@@ -621,9 +621,10 @@ hipError_t launch_feature_mask(const float* field, const int64_t* dims, int kind
 hipError_t launch_dilate_mask(const uint64_t* in, const int64_t* dims, int r, uint64_t* out,
                               hipStream_t st) {
   const int64_t W = (dims[0] + 63) / 64;
-  // two passes up to kZRadius (columns of words past 2^31 workgroups stay with one)
+  // two passes up to kZRadius (a thread per column of words: a launch holds fewer
+  // than 2^32 threads, so volumes of more columns stay with one pass)
   const bool two = r >= 1 && r <= kZRadius &&
-                   dims[3] * dims[1] * W < (int64_t)kBlock * 0x7fffffffLL;
+                   dims[3] * dims[1] * W <= ((int64_t)1 << 32) - kBlock;
   const int rz = two ? 0 : r;
   if (dims[1] * W <= kDilateLdsWords) {
     dilate_lds_kernel<<<(unsigned)(dims[3] * dims[2]), kBlock, (size_t)(dims[1] * W) * 8, st>>>(
