@@ -219,15 +219,17 @@ __device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t* s
 // block's total.
 constexpr int kRows = 64;
 __global__ void __launch_bounds__(256)
-    rows_kernel(GroupBuild G, const uint64_t* __restrict__ C, uint64_t* __restrict__ bits,
-                uint32_t* __restrict__ row_count, uint64_t* __restrict__ partial) {
+    rows_kernel(GroupBuild G, int64_t first, const uint64_t* __restrict__ C,
+                uint64_t* __restrict__ bits, uint32_t* __restrict__ row_count,
+                uint64_t* __restrict__ partial) {
   __shared__ uint32_t sh[4][kRows];
   const LevelBuild& d = G.lv[blockIdx.y];
   const int64_t rows = (int64_t)d.rt * d.rz * d.ry;
-  if (blockIdx.x * (int64_t)kRows >= rows) return;  // uniform: a smaller level
+  const int64_t block = first + blockIdx.x;  // first: blocks of rows before this launch's
+  if (block * kRows >= rows) return;  // uniform: a smaller level
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t row = blockIdx.x * (int64_t)kRows + lane;
+  const int64_t row = block * kRows + lane;
   const bool valid = row < rows;
   const int64_t mine = valid ? row : rows - 1;  // every lane stays with its wave
   const int64_t tz = mine / d.ry, y = mine - tz * d.ry;
@@ -289,7 +291,7 @@ __global__ void __launch_bounds__(256)
     if (valid) row_count[d.row + row] = c;
     uint64_t total = c;
     for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
-    if (lane == 0) partial[d.blk + blockIdx.x] = total;
+    if (lane == 0) partial[d.blk + block] = total;
   }
 }
 
@@ -604,8 +606,11 @@ hipError_t launch_build_index(const fhash_grid_desc* g, const uint64_t* mask,
                        dim3(T), 0, st, G, X, Y);
     hipLaunchKernelGGL(or_t_kernel, dim3(grid_for(std::max(maxc, kLineThreads), T), n),
                        dim3(T), 0, st, G, Y, X);
-    hipLaunchKernelGGL(rows_kernel, dim3((unsigned)maxrows, n), dim3(256), 0, st, G, X, Y,
-                       row_count, partial);
+    // four threads to a row: 2^30 rows are 2^32 threads, which no launch holds
+    constexpr int64_t kRowBlocks = (int64_t)1 << 23;
+    for (int64_t first = 0; first < maxrows; first += kRowBlocks)
+      hipLaunchKernelGGL(rows_kernel, dim3((unsigned)std::min(kRowBlocks, maxrows - first), n),
+                         dim3(256), 0, st, G, first, X, Y, row_count, partial);
     if (!bricks) {
       hipLaunchKernelGGL(scan_rows_kernel, dim3(n), dim3(1024), 0, st, G, partial, counts + l0);
       hipLaunchKernelGGL(entries_kernel,
