@@ -194,11 +194,14 @@ __global__ void __launch_bounds__(kBlock)
 
 // Cube dilation of radius r (0 <= r <= 63) inside each frame: a voxel is set
 // iff some set voxel lies within r along each of x, y and z.
-// One workgroup per (t, z) slice, as the isosurface pass; rz: the radius along z
-// (r, or 0 where dilate_z_kernel follows).
+// One workgroup per (t, z) slice, as the isosurface pass.  Z: along z too (false
+// where dilate_z_kernel follows; a radius along z as an argument of its own cost the
+// one-pass form 4 to 10 %).
+template <bool Z>
 __global__ void __launch_bounds__(kBlock)
     dilate_kernel(const uint64_t* __restrict__ in, int64_t Sx, int64_t Sy, int64_t Sz, int64_t W,
-                  int r, int rz, uint64_t* __restrict__ out) {
+                  int r, uint64_t* __restrict__ out) {
+  const int rz = Z ? r : 0;
   const int64_t slice = blockIdx.x;
   const int64_t z = slice % Sz;
   const int64_t frame_row0 = (slice - z) * Sy;
@@ -227,13 +230,15 @@ __global__ void __launch_bounds__(kBlock)
 }
 
 // The same dilation, separable inside a workgroup: pass 1 ORs the x-dilated
-// rows of the z window into an LDS copy of the slice ((2 rz + 1) x 3 word loads
-// per word), pass 2 ORs the y window out of LDS.  Used when a slice fits
+// rows of the z window into an LDS copy of the slice ((2r + 1) x 3 word loads per
+// word, 3 without Z), pass 2 ORs the y window out of LDS.  Used when a slice fits
 // kDilateLdsWords.
 constexpr int kDilateLdsWords = 8192;  // 64 KiB of LDS
+template <bool Z>
 __global__ void __launch_bounds__(kBlock)
     dilate_lds_kernel(const uint64_t* __restrict__ in, int64_t Sx, int64_t Sy, int64_t Sz,
-                      int64_t W, int r, int rz, uint64_t* __restrict__ out) {
+                      int64_t W, int r, uint64_t* __restrict__ out) {
+  const int rz = Z ? r : 0;
   extern __shared__ uint64_t zx[];  // [Sy][W]
   const int64_t slice = blockIdx.x;
   const int64_t z = slice % Sz;
@@ -312,6 +317,28 @@ void launch_dilate_z(uint64_t* io, const int64_t* dims, int64_t W, int r, hipStr
   } else if constexpr (R < kZRadius) {
     launch_dilate_z<R + 1>(io, dims, W, r, st);
   }
+}
+
+// Whether the z part goes as a pass of its own.  That pass is a launch, a chain of
+// Sz / 8 steps of about 0.75 us and the mask read and written once more (2.7 ps a
+// word); it takes away 2r more slices read by every workgroup of the first pass,
+// about 1.1 us per radius, 256 words of a slice and round of workgroups on the chip.
+// Both in ns, from one and two passes measured at r = 1, 2, 3, 4, 8 (us, one / two):
+// 100x100x100x10 8.1 8.0 9.0 10.6 20 / 17 18 19 20 23; 200x200x100x10 11 17 23 29 59 /
+// 22 23 25 26 31; 240x360x60x50 34 51 69 90 215 / 36 38 41 43 54; 480x720x120x24 163
+// 264 376 492 1071 / 132 144 155 166 209; 64x2000x10x10 12 17 22 29 42 / 12 13 14 15
+// 19.  Slices past the LDS copy read 3 (2r + 1)^2 words a word in one pass
+// (1000x1000x20x2: 141 514 1303 / 62 97 141).  A thread per column of words, and a
+// launch holds fewer than 2^32 threads.
+bool dilate_in_two_passes(const int64_t* dims, int64_t W, int r) {
+  const int64_t slice = dims[1] * W, slices = dims[3] * dims[2];
+  if (r < 1 || r > kZRadius || dims[3] * slice > ((int64_t)1 << 32) - kBlock) return false;
+  if (slice > kDilateLdsWords) return true;
+  const int64_t fit = 160 * 1024 / (slice * 8);  // workgroups of a CU
+  const int64_t resident = 256 * (fit < 8 ? fit : 8);
+  const int64_t rounds = (slices + resident - 1) / resident;
+  const int64_t saved = 1100 * r * ((slice + kBlock - 1) / kBlock) * rounds;
+  return saved > 5000 + 94 * dims[2] + slice * slices * 27 / 10000;
 }
 
 __global__ void box_init_kernel(int32_t* box, int64_t rows, int32_t Sx, int32_t Sy, int32_t Sz) {
@@ -621,17 +648,15 @@ hipError_t launch_feature_mask(const float* field, const int64_t* dims, int kind
 hipError_t launch_dilate_mask(const uint64_t* in, const int64_t* dims, int r, uint64_t* out,
                               hipStream_t st) {
   const int64_t W = (dims[0] + 63) / 64;
-  // two passes up to kZRadius (a thread per column of words: a launch holds fewer
-  // than 2^32 threads, so volumes of more columns stay with one pass)
-  const bool two = r >= 1 && r <= kZRadius &&
-                   dims[3] * dims[1] * W <= ((int64_t)1 << 32) - kBlock;
-  const int rz = two ? 0 : r;
+  const bool two = dilate_in_two_passes(dims, W, r);
+  const unsigned slices = (unsigned)(dims[3] * dims[2]);
   if (dims[1] * W <= kDilateLdsWords) {
-    dilate_lds_kernel<<<(unsigned)(dims[3] * dims[2]), kBlock, (size_t)(dims[1] * W) * 8, st>>>(
-        in, dims[0], dims[1], dims[2], W, r, rz, out);
+    const size_t lds = (size_t)(dims[1] * W) * 8;
+    auto kern = two ? dilate_lds_kernel<false> : dilate_lds_kernel<true>;
+    kern<<<slices, kBlock, lds, st>>>(in, dims[0], dims[1], dims[2], W, r, out);
   } else {
-    dilate_kernel<<<(unsigned)(dims[3] * dims[2]), kBlock, 0, st>>>(in, dims[0], dims[1], dims[2],
-                                                                    W, r, rz, out);
+    auto kern = two ? dilate_kernel<false> : dilate_kernel<true>;
+    kern<<<slices, kBlock, 0, st>>>(in, dims[0], dims[1], dims[2], W, r, out);
   }
   if (two) launch_dilate_z<1>(out, dims, W, r, st);
   return hipGetLastError();
