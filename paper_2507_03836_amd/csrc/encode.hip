@@ -13,43 +13,118 @@ namespace fh {
 
 namespace {
 
-// One thread per sample and level, levels fastest: the lookups of a sample's
-// levels overlap, and the threads of a wave write one contiguous range of enc
-// (a thread per sample with a loop over the levels wrote F floats per line).
-template <int F, typename T, bool BRICK>
+// How a launch walks the samples and levels.
+//  0: one thread per sample and level, levels fastest: the lookups of a sample's
+//     levels overlap and a wave writes one contiguous range of enc.
+//  > 0: one thread per sample and level, that many workgroups of 256 samples
+//     through one level after another, then the next as many: the waves in flight
+//     share a level and its part of the table stays in the caches.
+//  < 0: one thread per sample with a loop over its levels.
+struct Walk {
+  int chunk;
+  // workgroups for n samples of L levels
+  unsigned blocks(int64_t n, int L) const {
+    const int64_t b = (n + 255) / 256;
+    if (chunk == 0) return (unsigned)((n * L + 255) / 256);
+    return (unsigned)(chunk < 0 ? b : (b + chunk - 1) / chunk * chunk * L);
+  }
+  // the thread's sample, and its levels l0 .. l1 - 1
+  __device__ __forceinline__ int64_t at(int L, int& l0, int& l1) const {
+    if (chunk > 0) {
+      const unsigned group = blockIdx.x / (unsigned)(chunk * L);
+      const unsigned in = blockIdx.x - group * (unsigned)(chunk * L);
+      l0 = (int)(in / (unsigned)chunk);
+      l1 = l0 + 1;
+      return ((int64_t)group * chunk + (in - (unsigned)l0 * chunk)) * 256 + threadIdx.x;
+    }
+    const int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (chunk < 0) {
+      l0 = 0;
+      l1 = L;
+      return t;
+    }
+    const int64_t s = t / L;
+    l0 = (int)(t - s * L);
+    l1 = l0 + 1;
+    return s;
+  }
+};
+
+// Forward; row_bytes: of a table row.  us of a thread per sample / levels fastest /
+// level by level, 16 levels, F = 2, draw order:
+//                              100,003           262,144          1,048,576
+//   active, 240x360x60x50      309   300   259   821   780   621   3,395  3,076  2,356
+//   active, 121x90x61x20       195   238   167   535   610   383   2,337  2,409  1,451
+//   dense, 240x360x60x50       233   219   211   534   546   504   2,118  2,136  1,927
+//   hashed, 2^19 rows a level  147   200   117   282   504   238   1,082  1,975    849
+//   bricks, 240x360x60x50      314   380   350   826   961   781   3,637  3,653  2,798
+//   dense, fold 2, 8 levels     44    32    41    88    65    83     313    224    293
+// The table reads want level by level; the writes of enc, F floats of a line at a
+// time, want levels fastest, which wins where a batch is a few workgroups, from F = 4
+// on (8 levels, F = 8, 262,144 sorted samples 408 / 323 / 344; but of F = 4 a batch
+// of about one workgroup per CU on the smaller volume 113 / 121 / 104), on a dense
+// index of two features in cell order (359 / 311 / 347), and where the levels but the
+// largest fit the L2 of an XCD together (the last row).  A sample's lookups on bricks
+// are its longest part: a thread per sample from where every CU has one workgroup of
+// them (in cell order 100, 204 and 507 us there at F = 1, level by level 126, 220 and
+// 558).  On a dense or hashed index that holds only while no CU has a second one
+// (60,000 samples, hashed: 74.5 / 124 / 85).
+inline Walk fwd_walk(const GridDev& g, int64_t n, int64_t row_bytes) {
+  const int by_level = (int)((n + 255) / 256);
+  if (n <= 4096) return {0};
+  if (g.lv[0].brick) return {n > 40960 ? -1 : by_level};
+  if (g.active)
+    return {g.F <= 2 || (g.F == 4 && n > 40960 && n <= 131072) ? by_level : 0};
+  if (g.next_row && g.F >= 2) return {0};
+  const int64_t rows = g.last_pair + 2;
+  int64_t most = rows - g.lv[g.L - 1].slot_off;
+  for (int l = 0; l + 1 < g.L; ++l) {
+    const int64_t r = g.lv[l + 1].slot_off - g.lv[l].slot_off;
+    if (r > most) most = r;
+  }
+  if ((rows - most) * row_bytes <= 4 << 20) return {0};
+  return {n > 40960 && n <= 65536 ? -1 : by_level};
+}
+
+// Backward: levels fastest.
+inline Walk bwd_walk(const GridDev&, int64_t) { return {0}; }
+
+// LOOP: walk.chunk < 0 (as a loop of one trip the others lost up to 7 %).
+template <int F, typename T, bool BRICK, bool LOOP>
 __global__ void __launch_bounds__(256)
-    encode_fwd_kernel(GridDev g, const float4* __restrict__ pos, int64_t n,
+    encode_fwd_kernel(GridDev g, Walk walk, const float4* __restrict__ pos, int64_t n,
                       const T* __restrict__ table, float* __restrict__ enc) {
   __shared__ LevelDev lv[FHASH_MAX_LEVELS];
   if (threadIdx.x < FHASH_MAX_LEVELS) lv[threadIdx.x] = g.lv[threadIdx.x];
   __syncthreads();
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= n * g.L) return;
-  const int64_t s = t / g.L;
-  const int l[1] = {(int)(t - s * g.L)};
-  float out[1][F];
-  if constexpr (BRICK)
-    encode_level<F, T, true>(lv[l[0]], g.dir, g.active != 0, pos[s], table, out[0], g.tmask);
-  else
-    encode_rows<1, F, T>(g, lv, l, pos[s], table, out);
-  float* o = enc + t * F;
+  int l0, l1;
+  const int64_t s = walk.at(g.L, l0, l1);
+  if (s >= n) return;
+  const float4 p = pos[s];
+  float* o = enc + (s * g.L + l0) * F;
+  for (int i = l0; i < l1; ++i, o += F) {
+    const int l[1] = {i};
+    float out[1][F];
+    if constexpr (BRICK)
+      encode_level<F, T, true>(lv[i], g.dir, g.active != 0, p, table, out[0], g.tmask);
+    else
+      encode_rows<1, F, T>(g, lv, l, p, table, out);
 #pragma unroll
-  for (int k = 0; k < F; ++k) o[k] = out[0][k];
+    for (int k = 0; k < F; ++k) o[k] = out[0][k];
+    if constexpr (!LOOP) break;
+  }
 }
 
-// Rows order: one thread per sample and level, levels fastest, in groups of 2F
-// that add their members' samples one after another (scatter_rows); levels
-// below g.coarse are left to the LDS scatter.  Brick order: 2F threads per
-// sample (pair element x feature), a loop over the levels.
+// Rows order: one thread per sample and level in groups of 2F that add their
+// members' samples one after another (scatter_rows); levels below g.coarse are left
+// to the LDS scatter.  Brick order: 2F threads per sample (pair element x feature),
+// a loop over the levels.
 template <int F, bool BRICK>
 __global__ void __launch_bounds__(256)
-    encode_bwd_kernel(GridDev g, const float4* __restrict__ pos, int64_t n,
+    encode_bwd_kernel(GridDev g, Walk walk, const float4* __restrict__ pos, int64_t n,
                       const float* __restrict__ d_enc, float* __restrict__ d_table) {
-  __shared__ LevelDev lv[FHASH_MAX_LEVELS];
-  if (threadIdx.x < FHASH_MAX_LEVELS) lv[threadIdx.x] = g.lv[threadIdx.x];
-  __syncthreads();
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if constexpr (BRICK) {
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     constexpr int Q = 2 * F;
     const int64_t s = t / Q;
     if (s >= n) return;
@@ -57,11 +132,14 @@ __global__ void __launch_bounds__(256)
     const float4 p = pos[s];
     const float* gin = d_enc + s * (int64_t)g.L * F;
     for (int l = 0; l < g.L; ++l)
-      scatter_brick_lane<F>(lv[l], g.dir, g.active != 0, p, e, f, gin[l * F + f], d_table,
+      scatter_brick_lane<F>(g.lv[l], g.dir, g.active != 0, p, e, f, gin[l * F + f], d_table,
                             g.touch, g.touch_begin, g.gmask);
   } else {
-    const int64_t s = t / g.L;
-    const int l = (int)(t - s * g.L);
+    __shared__ LevelDev lv[FHASH_MAX_LEVELS];
+    if (threadIdx.x < FHASH_MAX_LEVELS) lv[threadIdx.x] = g.lv[threadIdx.x];
+    __syncthreads();
+    int l, l1;
+    const int64_t s = walk.at(g.L, l, l1);
     const bool own = s < n && l >= g.coarse;
     float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
     float gr[F];
@@ -70,7 +148,7 @@ __global__ void __launch_bounds__(256)
     if (own) {
       p = pos[s];
 #pragma unroll
-      for (int k = 0; k < F; ++k) gr[k] = d_enc[t * F + k];
+      for (int k = 0; k < F; ++k) gr[k] = d_enc[(s * g.L + l) * F + k];
     }
     scatter_rows<F>(g, lv[l], p, own, gr, d_table);
   }
@@ -137,14 +215,15 @@ inline int64_t launch_piece(int per) { return ((int64_t)1 << 31) / per; }
 template <int F, typename T>
 void launch_fwd_tt(const GridDev& g, const float* pos, int64_t n, const T* table, float* enc,
                    hipStream_t st) {
-  const dim3 grid((unsigned)((n * g.L + 255) / 256));
+  const Walk walk = fwd_walk(g, n, F * sizeof(T));
+  const dim3 grid(walk.blocks(n, g.L));
   const float4* p = reinterpret_cast<const float4*>(pos);
-  if (g.lv[0].brick)
-    hipLaunchKernelGGL((encode_fwd_kernel<F, T, true>), grid, dim3(256), 0, st, g, p, n, table,
-                       enc);
-  else
-    hipLaunchKernelGGL((encode_fwd_kernel<F, T, false>), grid, dim3(256), 0, st, g, p, n, table,
-                       enc);
+  const bool brick = g.lv[0].brick;
+  auto kern = walk.chunk < 0 ? (brick ? encode_fwd_kernel<F, T, true, true>
+                                      : encode_fwd_kernel<F, T, false, true>)
+                             : (brick ? encode_fwd_kernel<F, T, true, false>
+                                      : encode_fwd_kernel<F, T, false, false>);
+  hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, g, walk, p, n, table, enc);
 }
 
 template <int F>
@@ -173,12 +252,13 @@ hipError_t launch_bwd_t(const GridDev& g, const float* pos, int64_t n, const flo
     const int64_t m = n - s < piece ? n - s : piece;
     const float4* p = reinterpret_cast<const float4*>(pos) + s;
     const float* de = d_enc + s * g.L * F;
-    const dim3 grid((unsigned)((m * per + 255) / 256));
+    const Walk walk = bwd_walk(g, m);
+    const dim3 grid(brick ? (unsigned)((m * per + 255) / 256) : walk.blocks(m, g.L));
     if (brick)
-      hipLaunchKernelGGL((encode_bwd_kernel<F, true>), grid, dim3(256), 0, st, g, p, m, de,
+      hipLaunchKernelGGL((encode_bwd_kernel<F, true>), grid, dim3(256), 0, st, g, walk, p, m, de,
                          d_table);
     else
-      hipLaunchKernelGGL((encode_bwd_kernel<F, false>), grid, dim3(256), 0, st, g, p, m, de,
+      hipLaunchKernelGGL((encode_bwd_kernel<F, false>), grid, dim3(256), 0, st, g, walk, p, m, de,
                          d_table);
     if (const hipError_t err = hipGetLastError()) return err;
   }
