@@ -1,0 +1,38 @@
+"""Claim flags of the deferred Adam set in one call, whose launch on bricks has a loop
+over the levels from 131,073 samples on, against the same batch in calls of 5,000,
+which have a grid row per level: the same bytes."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_03836_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bricks", [False, True])
+@pytest.mark.parametrize("n", [131072, 131073])
+def test_flags(n, bricks):
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2507_03836_amd import _lib as fl
+    fl.lib()
+    dims, F = [70, 40, 30, 6], 2
+    res = [[3, 3, 3, 2], [9, 8, 7, 3], [33, 20, 17, 4], [70, 40, 30, 6]]
+    m = (np.random.default_rng(2).random(dims[::-1]) < 0.002).astype(np.uint8)
+    bits = torch.from_numpy(synth.pack_mask_rows(m).view(np.int64)).cuda()
+    lay = fl.LAYOUT_BRICKS if bricks else fl.LAYOUT_ROWS
+    idx, _, _keep, _ = fl.fhash_build_index(fl.grid_desc(res, F, lay), bits, dims)
+    begin = int(idx.slot_offset[1]) * F // 16 * 16
+    end = int(idx.slot_offset[len(res)]) * F // 16 * 16
+    arrays = [torch.zeros(end + 64, device="cuda") for _ in range(4)]
+    pos = torch.rand(n, 4, device="cuda", generator=torch.Generator(device="cuda").manual_seed(n))
+    ws = []
+    for step in (n, 5000):
+        lz = fl.LazyState(begin, end, 16)
+        for i in range(0, n, step):
+            part = pos[i:i + step]
+            fl.fhash_lazy_prepare(idx, part, len(part), lz, *arrays, phases=fl.LAZY_MARK)
+        ws.append(lz.ws.clone())
+    clean = fl.LazyState(begin, end, 16).ws
+    assert torch.equal(ws[0], ws[1]) and (ws[0] != clean).sum() > (end - begin) // 64
