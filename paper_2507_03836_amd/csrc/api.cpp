@@ -1081,14 +1081,19 @@ int fhash_render(const fhash_index* idx, const fhash_mlp_desc* mlp, const void* 
   // iterations are launched without waiting for one another; the host looks
   // every kLook of them whether a ray is left (an iteration past the end is
   // three launches that find nothing to do, about 8 us; looking cost 2 waits, 2
-  // copies and 2 fills per iteration, 1.0 of the 2.0 ms of a 200x150 image).
-  constexpr int kLook = 4;
+  // copies and 2 fills per iteration, 1.0 of the 2.0 ms of a 200x150 image).  The
+  // launches past the end are sized for the rays at the last look, so a large image
+  // looks after its first iteration too: where nothing of the feature is in view that
+  // one is all there is (1920x1080, nothing but a few voxels set, 294 us with the
+  // host in every iteration, 334 looking at the fourth, 286 so).
+  constexpr int kLook = 4, kLookFirst = 1 << 17;
+  int look = st.n_alive >= kLookFirst ? 1 : kLook;
   const int32_t* count = fh::render_sample_count(ws, W, H);
   int32_t alive = (int32_t)st.n_alive;
   int cur = 0;
   while (alive > 0) {
     const int64_t most = std::min(NR, (int64_t)opts->arm_max * alive);  // samples per iteration
-    for (int k = 0; k < kLook; ++k, cur = 1 - cur) {
+    for (int k = 0; k < look; ++k, cur = 1 - cur) {
       hipError_t e = fh::launch_render_march_next(ws, W, H, dims, st.t01, opts->ds,
                                                   opts->max_steps, opts->arm_max, cur, alive, pos,
                                                   S(stream));
@@ -1106,6 +1111,7 @@ int fhash_render(const fhash_index* idx, const fhash_mlp_desc* mlp, const void* 
     const hipError_t e = fh::render_progress(ws, W, H, cur, &alive, &st.samples, &st.iterations,
                                              S(stream));
     if (e != hipSuccess) return hip_status(e, "fhash_render");
+    look = kLook;
   }
   if (stats) {
     stats->iterations = st.iterations;
