@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(256)
     const int l[1] = {i};
     float out[1][F];
     if constexpr (BRICK)
-      encode_level<F, T, true>(lv[i], g.dir, g.active != 0, p, table, out[0], g.tmask);
+      encode_brick_level<F, T>(lv[i], g.dir, g.active != 0, p, table, out[0], g.tmask);
     else
       encode_rows<1, F, T>(g, lv, l, p, table, out);
 #pragma unroll

@@ -200,15 +200,16 @@ __device__ __forceinline__ void encode_rows(const GridDev& g, const LevelDev* lv
   }
 }
 
-// Forward of one level for one sample: out[k] = sum_c w_c E[slot_c][k].
-// Invalid (inactive) corners get weight 0 and read row 0, so every load is
-// unconditional.  Brick order; the rows order goes through encode_rows.
+// Forward of one brick-ordered level for one sample: out[k] = sum_c w_c
+// E[slot_c][k].  Invalid (inactive) corners get weight 0 and read row 0, so every
+// load is unconditional.  (The rows order goes through encode_rows.)
 // Requires a table with at least one row.  tmask: the table's run mask
 // (run_off; F divides 16, so a row never straddles a run).
-template <int F, typename T, bool BRICK = false>
-__device__ __forceinline__ void encode_level(const LevelDev& d, const ulonglong2* dir, bool active,
-                                             const float4 p, const T* __restrict__ table,
-                                             float* out, int64_t tmask) {
+template <int F, typename T>
+__device__ __forceinline__ void encode_brick_level(const LevelDev& d, const ulonglong2* dir,
+                                                   bool active, const float4 p,
+                                                   const T* __restrict__ table, float* out,
+                                                   int64_t tmask) {
   int ix, iy, iz, it;
   float fx, fy, fz, ft;
   locate(p.x, d.rx, d.sx, ix, fx);
@@ -218,14 +219,14 @@ __device__ __forceinline__ void encode_level(const LevelDev& d, const ulonglong2
   float acc[F];
 #pragma unroll
   for (int k = 0; k < F; ++k) acc[k] = 0.0f;
-  const int a = pair_axis<BRICK>(ix, iy, iz, it);
+  const int a = pair_axis<true>(ix, iy, iz, it);
   const float fa = pair_frac(a, fx, fy, fz, ft);
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     float wr;
     int64_t s0, s1;
     bool v0, v1;
-    corner_pair<BRICK>(d, dir, active, ix, iy, iz, it, fx, fy, fz, ft, a, r, s0, s1, v0, v1, wr);
+    corner_pair<true>(d, dir, active, ix, iy, iz, it, fx, fy, fz, ft, a, r, s0, s1, v0, v1, wr);
     float e0[F], e1[F];
     RowLoad<F, T>::load(table, run_off((v0 ? s0 : 0) * F, tmask), e0);
     RowLoad<F, T>::load(table, run_off((v1 ? s1 : 0) * F, tmask), e1);

@@ -61,7 +61,7 @@ __device__ __forceinline__ void gather_block(const GridDev& g, const LevelDev* l
         const int l = (16 * a + 4 * grp) / F + j;
         float e[F];
         if (valid && l < g.L) {
-          encode_level<F, T, true>(lv[l], g.dir, g.active != 0, p, table, e, g.tmask);
+          encode_brick_level<F, T>(lv[l], g.dir, g.active != 0, p, table, e, g.tmask);
         } else {
 #pragma unroll
           for (int k = 0; k < F; ++k) e[k] = 0.0f;
