@@ -7,7 +7,10 @@
 // axis.  That is separable, so a level's vertex bits come from one OR over
 // voxel ranges per axis: along y (usually the axis a level shrinks most, so the
 // later passes have the least to read), along z and t (vertex v = cell v-1 OR
-// cell v, each voxel read once per thread), and along x inside the words.
+// cell v, each voxel read once per thread), and along x inside the words.  Where the
+// workspace is not to hold the whole mask transposed, it goes through the first three
+// a slab of frames at a time, and the pass along t adds each slab's frames to the
+// vertices they reach.
 //
 // The mask is first transposed to [t][z][word][y], the store order of the
 // directory, so that neighbouring threads of every pass hold neighbouring y:
@@ -68,13 +71,15 @@ struct Steps {
 // part of each workspace array begins (64-bit words; row counts; row blocks).
 struct LevelBuild {
   int32_t rx, ry, rz, rt, wv, y0;  // y0: ry of the group's levels before this one
-  int64_t a, b, c, bits;
+  int32_t v0, v1;                  // the t vertices that the slab's frames reach
+  int64_t a, b, c, bits;           // a, b: words per frame of the slab
   int64_t row, blk, dir;
 };
 constexpr int kMaxGroup = FHASH_MAX_LEVELS;
 struct GroupBuild {
   LevelBuild lv[kMaxGroup];
   int64_t Sx, Sy, Sz, St, Wm;
+  int64_t f0, nf;  // the slab: frames f0 .. f0 + nf - 1
 };
 
 // Mask rows [t][z][y][w] -> [t][z][w][y], 64 y by up to 32 words at a time
@@ -110,13 +115,16 @@ __global__ void __launch_bounds__(256)
 // one cell of its neighbour's again) until 2^20 threads share the work: the z
 // pass of the 480x720x120x24 volume's levels took 427 us at 2^18 and 332 us so.
 constexpr int64_t kLineThreads = 1 << 20;
+__host__ __device__ inline int64_t line_chunks(int64_t lines, int64_t R) {
+  const int64_t chunks = lines >= kLineThreads ? 1 : (kLineThreads + lines - 1) / lines;
+  return chunks < (R + 3) / 4 ? chunks : (R + 3) / 4;
+}
 __device__ __forceinline__ void or_axis(const uint64_t* __restrict__ in,
                                         uint64_t* __restrict__ out, int64_t outer, int64_t S,
                                         int64_t R, int64_t inner) {
   // vertices per thread: fewer where (outer, inner) alone leaves the chip idle
   const int64_t lines = outer * inner;
-  int64_t chunks = lines >= kLineThreads ? 1 : (kLineThreads + lines - 1) / lines;
-  if (chunks > (R + 3) / 4) chunks = (R + 3) / 4;
+  const int64_t chunks = line_chunks(lines, R);
   const int64_t per = (R + chunks - 1) / chunks, total = lines * chunks;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
@@ -150,7 +158,7 @@ __device__ __forceinline__ void or_axis(const uint64_t* __restrict__ in,
 __global__ void __launch_bounds__(256)
     or_y_kernel(GroupBuild G, int32_t items, const uint64_t* __restrict__ mask,
                 uint64_t* __restrict__ A) {
-  const int64_t lines = G.St * G.Sz * G.Wm;
+  const int64_t lines = G.nf * G.Sz * G.Wm;
   for (int64_t line = blockIdx.x; line < lines; line += gridDim.x) {
     const uint64_t* src = mask + line * G.Sy;
     int j = 0;
@@ -162,7 +170,7 @@ __global__ void __launch_bounds__(256)
       uint64_t acc = 0;
 #pragma unroll 4
       for (int64_t s = lo; s <= hi; ++s) acc |= src[s];
-      A[G.lv[j].a + line * R + v] = acc;
+      A[G.lv[j].a * G.nf + line * R + v] = acc;
     }
   }
 }
@@ -170,13 +178,49 @@ __global__ void __launch_bounds__(256)
 __global__ void __launch_bounds__(256)
     or_z_kernel(GroupBuild G, const uint64_t* __restrict__ A, uint64_t* __restrict__ B) {
   const LevelBuild& d = G.lv[blockIdx.y];
-  or_axis(A + d.a, B + d.b, G.St, G.Sz, d.rz, G.Wm * d.ry);
+  or_axis(A + d.a * G.nf, B + d.b * G.nf, G.nf, G.Sz, d.rz, G.Wm * d.ry);
 }
 
 __global__ void __launch_bounds__(256)
     or_t_kernel(GroupBuild G, const uint64_t* __restrict__ B, uint64_t* __restrict__ C) {
+  // Along t: the slab's part of vertices v0 .. v1 - 1, walked as or_axis does.  The
+  // slab that holds the first voxel of a vertex's range writes its word, later ones
+  // add to it.
   const LevelBuild& d = G.lv[blockIdx.y];
-  or_axis(B + d.b, C + d.c, 1, G.St, d.rt, d.rz * G.Wm * d.ry);
+  const int64_t inner = d.rz * G.Wm * d.ry, S = G.St, R = d.rt, nv = d.v1 - d.v0;
+  const int64_t f1 = G.f0 + G.nf;
+  const int64_t chunks = line_chunks(inner, nv);
+  const int64_t per = (nv + chunks - 1) / chunks, total = inner * chunks;
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
+       e += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t q = e % inner, va = d.v0 + e / inner * per;
+    const int64_t vb = va + per < d.v1 ? va + per : d.v1;
+    const uint64_t* src = B + d.b * G.nf + q;
+    uint64_t* dst = C + d.c + q;
+    int64_t c = va > 0 ? va - 1 : 0;
+    Steps top(c, S, R);
+    int64_t lo = top.q + (top.r > 0 ? 1 : 0), first = 0;  // first voxel of vertex c
+    uint64_t prev = 0;
+    for (; c < vb; ++c) {
+      uint64_t cell = 0;
+      const int64_t lo_c = lo;
+      if (c < R - 1) {
+        top.next();
+        int64_t hi = top.q < S - 1 ? top.q : S - 1;
+        if (hi > f1 - 1) hi = f1 - 1;
+#pragma unroll 4
+        for (int64_t s = lo_c > G.f0 ? lo_c : G.f0; s <= hi; ++s)
+          cell |= src[(s - G.f0) * inner];
+        lo = top.q + (top.r > 0 ? 1 : 0);
+      }
+      if (c >= va) {
+        const uint64_t w = prev | cell;
+        dst[c * inner] = first >= G.f0 ? w : dst[c * inner] | w;
+      }
+      prev = cell;
+      first = lo_c;
+    }
+  }
 }
 
 constexpr int kScanThreads = 256;
@@ -449,8 +493,8 @@ inline int grid_for(int64_t total, int threads) {
 }
 
 // Sizes of one level's parts of the workspace: a, b, c and bits in words (the
-// outputs of the passes along y, z, t and x), rows, row blocks, and the brick
-// directory.
+// outputs of the passes along y and z, per frame, along t and along x), rows, row
+// blocks, and the brick directory.
 struct LevelSizes {
   int64_t a, b, c, bits, rows, blk;
   int64_t Bx, By, Bz, Bt, Wb, bwords, bnb;  // brick layout
@@ -459,8 +503,8 @@ struct LevelSizes {
 LevelSizes level_sizes(const int32_t* r, const int64_t* dims) {
   LevelSizes s;
   const int64_t Wm = (dims[0] + 63) / 64, Wv = ((int64_t)r[0] + 63) / 64;
-  s.a = dims[3] * dims[2] * Wm * r[1];
-  s.b = dims[3] * r[2] * Wm * r[1];
+  s.a = dims[2] * Wm * r[1];
+  s.b = r[2] * Wm * r[1];
   s.c = (int64_t)r[3] * r[2] * Wm * r[1];
   s.rows = (int64_t)r[3] * r[2] * r[1];
   s.bits = s.rows * Wv;
@@ -489,67 +533,160 @@ int64_t index_dir_words(const fhash_grid_desc* g, int l) {
 
 namespace {
 
-// The workspace: the transposed mask, the arrays the passes alternate between
-// (y -> X, z -> Y, t -> X, x -> Y), row counts, block totals, level counts, and
-// the brick directory before its reordering.  Each is twice as large as the
-// level that needs most of it (kShare), so that the finest level goes alone
-// and the others in two or three groups: each group reads the mask once.
-constexpr int64_t kShare = 2;
-
-struct BuildWs {
-  int64_t mask, X, Y, rows, blk, bricks;  // words; rows in 4 bytes; bricks in 16
-  size_t bytes;
+// The plan of a build.  Levels go through the passes in groups, coarsest first: the
+// next levels that fit the arrays together (a brick level has them to itself), which
+// hold the largest level and up to as much again (share), so that the finest level
+// goes alone and the others in a few groups: each group reads the mask once.
+//
+// The workspace has row counts, block totals, level counts, the brick directory
+// before its reordering, and either
+//  - the whole mask transposed and two arrays that the passes alternate between (y ->
+//    X, z -> Y, t -> X, x -> Y), or
+//  - the words reduced along t (C) and one region for a slab of frames, transposed and
+//    reduced along y and z, and then for the vertex bits,
+// the second where the first would take more than a pass per axis over the whole mask
+// does for the largest level (its cells along t, along t and z, and the directory's
+// words twice) and more than kSmallBytes: levels much coarser than the volume, whose
+// transposed mask is most of it.  A slab is then as large as that bound leaves, at
+// least a frame.  480x720x120x100, 12 levels of up to 120x180x30x50: 2,874 us and 340
+// MB in slabs, 2,316 us and 899 MB whole (2,690 us and 473 MB a pass per axis).  With
+// arrays of twice the largest level throughout, 432x432x432x60 at its own resolution
+// took 8,110 us and 3,228 MB; within the bound 8,471 us and 2,415 MB.
+struct BuildPlan {
+  bool whole;
+  int groups;
+  int first[FHASH_MAX_LEVELS + 1];
+  int64_t frames;                             // of a slab
+  int64_t X, Y, rows, blk, bricks;            // words; rows in 4 bytes; bricks in 16
+  size_t bytes;                               // X, Y: C and the slab's region in slabs
 };
+constexpr size_t kSmallBytes = (size_t)256 << 20;
 
-BuildWs build_ws(const fhash_grid_desc* g, const int64_t* dims) {
-  BuildWs w{};
-  w.mask = dims[3] * dims[2] * dims[1] * ((dims[0] + 63) / 64);
+BuildPlan build_plan(const fhash_grid_desc* g, const int64_t* dims) {
+  const bool brick = g->layout == FHASH_LAYOUT_BRICKS;
+  const int64_t Wm = (dims[0] + 63) / 64, T = dims[3];
+  const int64_t mask = dims[2] * dims[1] * Wm;  // words of a frame
+  LevelSizes most{}, sizes[FHASH_MAX_LEVELS];
+  int64_t bound = 0;
   for (int l = 0; l < g->n_levels; ++l) {
-    const LevelSizes s = level_sizes(g->res[l], dims);
-    w.X = std::max(w.X, std::max(s.a, s.c));
-    w.Y = std::max(w.Y, std::max(s.b, s.bits));
-    w.rows = std::max(w.rows, s.rows);
-    w.blk = std::max(w.blk, s.blk);
-    if (g->layout == FHASH_LAYOUT_BRICKS) {
-      w.bricks = std::max(w.bricks, s.bwords);
-      w.blk = std::max(w.blk, s.bnb);
+    const int32_t* r = g->res[l];
+    const LevelSizes s = sizes[l] = level_sizes(r, dims);
+    most.a = std::max(most.a, s.a);
+    most.b = std::max(most.b, s.b);
+    most.c = std::max(most.c, s.c);
+    most.bits = std::max(most.bits, s.bits);
+    most.rows = std::max(most.rows, s.rows);
+    most.blk = std::max(most.blk, std::max(s.blk, brick ? s.bnb : 0));
+    most.bwords = std::max(most.bwords, brick ? s.bwords : 0);
+    bound = std::max(bound, (r[3] - 1) * mask + (int64_t)(r[3] - 1) * (r[2] - 1) * dims[1] * Wm +
+                                2 * s.bits);
+  }
+  BuildPlan p{};
+  p.bricks = most.bwords;
+  // capacities and groups with the arrays at share sixteenths of the largest level;
+  // returns the words per frame of the group that takes most of them
+  auto group = [&](bool whole, int share) {
+    const int64_t a = most.a * T * share / 16, b = most.b * T * share / 16;
+    const int64_t c = most.c * share / 16, bits = most.bits * share / 16;
+    p.whole = whole;
+    p.X = whole ? std::max(a, c) : c;
+    p.Y = whole ? std::max(b, bits) : bits;
+    p.rows = most.rows * share / 16;
+    p.blk = most.blk * share / 16;
+    p.groups = 0;
+    int64_t frame = 0;
+    for (int l = 0; l < g->n_levels;) {
+      LevelSizes t{};
+      p.first[p.groups++] = l;
+      for (int n = 0; l < g->n_levels; ++l, ++n) {
+        const LevelSizes& s = sizes[l];
+        if (n > 0 && (brick || t.c + s.c > p.X || t.bits + s.bits > p.Y ||
+                      t.rows + s.rows > p.rows || t.blk + s.blk > p.blk ||
+                      (whole && ((t.a + s.a) * T > p.X || (t.b + s.b) * T > p.Y))))
+          break;
+        t.a += s.a;
+        t.b += s.b;
+        t.c += s.c;
+        t.bits += s.bits;
+        t.rows += s.rows;
+        t.blk += s.blk;
+      }
+      frame = std::max(frame, mask + t.a + t.b);
     }
+    p.first[p.groups] = g->n_levels;
+    return frame;
+  };
+  auto total = [&] {
+    return align256((p.whole ? mask * T : 0) * 8) + align256(p.X * 8) + align256(p.Y * 8) +
+           align256(p.rows * 4) + align256(p.blk * 8) + align256(8 * FHASH_MAX_LEVELS) +
+           align256(p.bricks * 16);
+  };
+  const bool one = brick || g->n_levels == 1;
+  const size_t most_bytes = std::max((size_t)bound * 8 + p.bricks * 16, kSmallBytes);
+  for (int share = one ? 16 : 32; share >= 16; --share) {
+    group(true, share);
+    p.frames = T;
+    p.bytes = total();
+    if (p.bytes <= most_bytes) return p;
   }
-  if (g->layout != FHASH_LAYOUT_BRICKS && g->n_levels > 1) {
-    w.X *= kShare;
-    w.Y *= kShare;
-    w.rows *= kShare;
-    w.blk *= kShare;
+  for (int share = one ? 16 : 20; share >= 16; share -= 4) {
+    const int64_t frame = group(false, share);
+    const int64_t left = bound - p.X - p.rows / 2 - p.blk;
+    p.frames = std::max(std::min(left / frame, T), (int64_t)1);
+    p.Y = std::max(p.frames * frame, p.Y);
+    p.bytes = total();
+    if (p.Y <= left) break;
   }
-  w.bytes = align256(w.mask * 8) + align256(w.X * 8) + align256(w.Y * 8) + align256(w.rows * 4) +
-            align256(w.blk * 8) + align256(8 * FHASH_MAX_LEVELS) + align256(w.bricks * 16);
-  return w;
+  return p;
+}
+
+// The t vertices v0 .. v1 - 1 of a level that frames f0 .. f1 - 1 reach: those whose
+// voxel range (of the cells on either side) meets the slab, and those without a voxel
+// whose range would begin in it.
+void slab_vertices(int64_t S, int64_t R, int64_t f0, int64_t f1, int32_t* v0, int32_t* v1) {
+  auto first = [&](int64_t v) { return v > 0 ? ((v - 1) * (S - 1) + R - 2) / (R - 1) : 0; };
+  auto last = [&](int64_t v) {
+    return std::max(first(v), v < R - 1 ? std::min((v + 1) * (S - 1) / (R - 1), S - 1) : S - 1);
+  };
+  auto lower = [&](auto reached) {  // first v in [0, R] for which reached(v) holds
+    int64_t lo = 0, hi = R;
+    while (lo < hi) {
+      const int64_t m = (lo + hi) / 2;
+      if (reached(m)) hi = m;
+      else lo = m + 1;
+    }
+    return (int32_t)lo;
+  };
+  *v0 = lower([&](int64_t v) { return last(v) >= f0; });
+  *v1 = lower([&](int64_t v) { return first(v) >= f1; });
 }
 
 }  // namespace
 
 size_t index_workspace_bytes(const fhash_grid_desc* g, const int64_t* dims) {
-  return build_ws(g, dims).bytes;
+  return build_plan(g, dims).bytes;
 }
 
 hipError_t launch_build_index(const fhash_grid_desc* g, const uint64_t* mask,
                               const int64_t* dims, ulonglong2* dir, const int64_t* dir_off,
                               void* ws, uint64_t* counts_host, hipStream_t st) {
   const bool bricks = g->layout == FHASH_LAYOUT_BRICKS;
-  const BuildWs w = build_ws(g, dims);
+  const BuildPlan w = build_plan(g, dims);
   char* p = static_cast<char*>(ws);
   auto take = [&p](size_t bytes) {
     char* q = p;
     p += align256(bytes);
     return q;
   };
-  uint64_t* tmask = reinterpret_cast<uint64_t*>(take(w.mask * 8));
+  const int64_t frame = dims[2] * dims[1] * ((dims[0] + 63) / 64);  // words of the mask
+  uint64_t* whole = reinterpret_cast<uint64_t*>(take(w.whole ? frame * dims[3] * 8 : 0));
   uint64_t* X = reinterpret_cast<uint64_t*>(take(w.X * 8));
   uint64_t* Y = reinterpret_cast<uint64_t*>(take(w.Y * 8));
   uint32_t* row_count = reinterpret_cast<uint32_t*>(take(w.rows * 4));
   uint64_t* partial = reinterpret_cast<uint64_t*>(take(w.blk * 8));
   uint64_t* counts = reinterpret_cast<uint64_t*>(take(8 * FHASH_MAX_LEVELS));
   ulonglong2* bricked = reinterpret_cast<ulonglong2*>(take(w.bricks * 16));
+  uint64_t *C = X, *bits = Y;  // the passes along t and x write over what they no longer need
 
   const int T = 256;
   GroupBuild G{};
@@ -558,69 +695,71 @@ hipError_t launch_build_index(const fhash_grid_desc* g, const uint64_t* mask,
   G.Sz = dims[2];
   G.St = dims[3];
   G.Wm = (dims[0] + 63) / 64;
-  const int64_t tiles = G.St * G.Sz * ((G.Sy + 63) / 64) * ((G.Wm + kTileW - 1) / kTileW);
-  hipLaunchKernelGGL(transpose_kernel, dim3(grid_for(tiles, 1)), dim3(T), 0, st, mask, tmask,
-                     G.St * G.Sz, G.Sy, G.Wm);
-  int l0 = 0;
-  while (l0 < g->n_levels) {
-    // the next levels that fit the workspace together, coarsest first (a brick
-    // level has the brick arrays to itself)
-    int64_t a = 0, b = 0, c = 0, bits = 0, rows = 0, blk = 0, maxrows = 0, maxb = 0, maxc = 0;
-    int n = 0;
-    while (l0 + n < g->n_levels) {
-      const int32_t* r = g->res[l0 + n];
+  for (int k = 0; k < w.groups; ++k) {
+    const int l0 = w.first[k], n = w.first[k + 1] - l0;
+    int64_t a = 0, b = 0, c = 0, nbits = 0, rows = 0, maxrows = 0, blk = 0;
+    for (int j = 0; j < n; ++j) {
+      const int32_t* r = g->res[l0 + j];
       const LevelSizes s = level_sizes(r, dims);
-      if (n > 0 && (bricks || std::max(a + s.a, c + s.c) > w.X ||
-                    std::max(b + s.b, bits + s.bits) > w.Y || rows + s.rows > w.rows ||
-                    blk + s.blk > w.blk))
-        break;
-      LevelBuild& d = G.lv[n];
+      LevelBuild& d = G.lv[j];
       d.rx = r[0];
       d.ry = r[1];
       d.rz = r[2];
       d.rt = r[3];
       d.wv = (r[0] + 63) / 64;
-      d.y0 = n == 0 ? 0 : G.lv[n - 1].y0 + G.lv[n - 1].ry;
+      d.y0 = j == 0 ? 0 : G.lv[j - 1].y0 + G.lv[j - 1].ry;
       d.a = a;
       d.b = b;
       d.c = c;
-      d.bits = bits;
+      d.bits = nbits;
       d.row = rows;
       d.blk = blk;
-      d.dir = dir_off[l0 + n];
+      d.dir = dir_off[l0 + j];
       a += s.a;
       b += s.b;
       c += s.c;
-      bits += s.bits;
+      nbits += s.bits;
       rows += s.rows;
       blk += s.blk;
       maxrows = std::max(maxrows, s.blk);
-      maxb = std::max(maxb, s.b / r[2]);
-      maxc = std::max(maxc, s.c / r[3]);
-      ++n;
     }
-    // or_axis: a thread per line, or kLineThreads where the lines are fewer
-    hipLaunchKernelGGL(or_y_kernel, dim3(grid_for(G.St * G.Sz * G.Wm, 1)), dim3(T), 0, st, G,
-                       G.lv[n - 1].y0 + G.lv[n - 1].ry, tmask, X);
-    hipLaunchKernelGGL(or_z_kernel, dim3(grid_for(std::max(maxb, kLineThreads), T), n),
-                       dim3(T), 0, st, G, X, Y);
-    hipLaunchKernelGGL(or_t_kernel, dim3(grid_for(std::max(maxc, kLineThreads), T), n),
-                       dim3(T), 0, st, G, Y, X);
+    for (G.f0 = 0; G.f0 < G.St; G.f0 += G.nf) {
+      G.nf = std::min(w.frames, G.St - G.f0);
+      uint64_t* tmask = w.whole ? whole : Y;
+      uint64_t* A = w.whole ? X : tmask + G.nf * frame;
+      uint64_t* B = w.whole ? Y : A + G.nf * a;
+      int64_t zt = 1, tt = 1;  // threads of the passes along z and t, of the level with most
+      for (int j = 0; j < n; ++j) {
+        LevelBuild& d = G.lv[j];
+        slab_vertices(G.St, d.rt, G.f0, G.f0 + G.nf, &d.v0, &d.v1);
+        const int64_t zl = G.nf * G.Wm * d.ry, tl = d.rz * G.Wm * d.ry;
+        zt = std::max(zt, zl * line_chunks(zl, d.rz));
+        tt = std::max(tt, tl * line_chunks(tl, d.v1 - d.v0));
+      }
+      const int64_t tiles = G.nf * G.Sz * ((G.Sy + 63) / 64) * ((G.Wm + kTileW - 1) / kTileW);
+      if (!w.whole || k == 0)
+        hipLaunchKernelGGL(transpose_kernel, dim3(grid_for(tiles, 1)), dim3(T), 0, st,
+                           mask + G.f0 * frame, tmask, G.nf * G.Sz, G.Sy, G.Wm);
+      hipLaunchKernelGGL(or_y_kernel, dim3(grid_for(G.nf * G.Sz * G.Wm, 1)), dim3(T), 0, st, G,
+                         G.lv[n - 1].y0 + G.lv[n - 1].ry, tmask, A);
+      hipLaunchKernelGGL(or_z_kernel, dim3(grid_for(zt, T), n), dim3(T), 0, st, G, A, B);
+      hipLaunchKernelGGL(or_t_kernel, dim3(grid_for(tt, T), n), dim3(T), 0, st, G, B, C);
+    }
     // four threads to a row: 2^30 rows are 2^32 threads, which no launch holds
     constexpr int64_t kRowBlocks = (int64_t)1 << 23;
     for (int64_t first = 0; first < maxrows; first += kRowBlocks)
       hipLaunchKernelGGL(rows_kernel, dim3((unsigned)std::min(kRowBlocks, maxrows - first), n),
-                         dim3(256), 0, st, G, first, X, Y, row_count, partial);
+                         dim3(256), 0, st, G, first, C, bits, row_count, partial);
     if (!bricks) {
       hipLaunchKernelGGL(scan_rows_kernel, dim3(n), dim3(1024), 0, st, G, partial, counts + l0);
       hipLaunchKernelGGL(entries_kernel,
                          dim3((unsigned)((maxrows + kScanThreads / kRows - 1) /
                                          (kScanThreads / kRows)), n),
-                         dim3(kScanThreads), 0, st, G, Y, row_count, partial, dir);
+                         dim3(kScanThreads), 0, st, G, bits, row_count, partial, dir);
     } else {
       const int32_t* r = g->res[l0];
       const LevelSizes s = level_sizes(r, dims);
-      hipLaunchKernelGGL(brickify_kernel, dim3(grid_for(s.bwords, T)), dim3(T), 0, st, Y, bricked,
+      hipLaunchKernelGGL(brickify_kernel, dim3(grid_for(s.bwords, T)), dim3(T), 0, st, bits, bricked,
                          (int64_t)r[0], (int64_t)r[1], (int64_t)r[2], (int64_t)r[3],
                          (int64_t)G.lv[0].wv, s.Wb, s.By, s.Bz, s.bwords);
       hipLaunchKernelGGL(popc_block_sums_kernel, dim3((unsigned)s.bnb), dim3(kScanThreads), 0, st,
@@ -632,7 +771,6 @@ hipError_t launch_build_index(const fhash_grid_desc* g, const uint64_t* mask,
       hipLaunchKernelGGL(dir_interleave_kernel, dim3(grid_for(s.bwords, T)), dim3(T), 0, st,
                          bricked, dir + dir_off[l0], s.Bt * s.Bz * s.By, s.By, s.Wb);
     }
-    l0 += n;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
