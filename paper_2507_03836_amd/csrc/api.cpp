@@ -173,6 +173,10 @@ static int apply_touch(const fhash_touch* t, int64_t len, fh::GridDev* g) {
 // 1234, 1241; mixed 2^20 8786, 8678, 8620; with two workgroups of the scatter per
 // CU, four and eight: 3091 and 3112; 1236 and 1239; 8587 and 8485; 300,000 samples
 // 3479 and 3494; F = 1 2453 and 2410.  F = 4, 8 levels, one and two 2074 and 2122.
+// A batch in draw order, which the flag does not suit, pays for boxes past the image
+// (fused call of 2^18, 2^20 samples, F = 2, 16 levels: 2,411 and 9,630 us with the
+// flag, 2,134 and 8,196 without; with one cell per sample and float atomics in LDS
+// the flag took 2,708 and 10,643).
 // In any batch: levels so small that their whole vertex box
 // fits the LDS image and that every vertex takes 16 or more corners' adds
 // (n >= vertices): atomics into one 64-byte line are performed one after

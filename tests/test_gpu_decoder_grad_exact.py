@@ -1,7 +1,7 @@
 """The decoder gradient of the fused backward under contention: integer weights,
 inputs and output gradients, so that every sum is exact in FP32 in any order and
 an add that the waves of a workgroup lose between them shows.  The reference is
-the same network in 64-bit integers; the sums' magnitudes are held below 2^24."""
+the same network on whole numbers in FP64; the sums' magnitudes are held below 2^24."""
 import numpy as np
 import pytest
 import torch
@@ -51,11 +51,12 @@ def _reference(cell, table, layers, dy):
 def test_no_add_is_lost(fl, n, hidden, nh, dt):
     rng = np.random.default_rng(n + hidden + nh)
     cell = rng.integers(0, 2, (n, 4))
-    table = [_sparse(rng, (81, F)) for _ in range(L)]
+    table = [_sparse(rng, (81, F)).astype(np.float64) for _ in range(L)]
     width = [L * F] + [hidden] * nh + [1]
-    layers = [(_sparse(rng, (o, i)), _sparse(rng, (o,))) for i, o in zip(width, width[1:])]
+    layers = [(_sparse(rng, (o, i)).astype(np.float64), _sparse(rng, (o,)).astype(np.float64))
+              for i, o in zip(width, width[1:])]
     layers[-1][0][:, ::2] = 1
-    dy = rng.integers(-1, 2, n)
+    dy = rng.integers(-1, 2, n).astype(np.float64)
     y, ref, mag = _reference(cell, table, layers, dy)
     assert mag.max() < 2 ** 24 and np.abs(y).max() < 2 ** 24 and (ref != 0).sum() > ref.size // 8
     idx = fl.fhash_dense_index(fl.grid_desc(RES, F))[0]
