@@ -53,8 +53,8 @@ ADAM_RW_BYTES_PER_PARAM = 24
 # rocprofv3 FETCH_SIZE (x2.000) and WRITE_SIZE (x1.000) passes scaled by a plain streaming
 # copy of known size; valid only for the parameter count, optimiser state layout and
 # optimizer source they were taken on.
-ADAM_TRAFFIC = {"bytes": 160.80e9, "params": 6390343593, "moments": "with-params",
-                "source_md5": "f6d69b782465363a0baa0efdebaf6158"}
+ADAM_TRAFFIC = {"bytes": 160.72e9, "params": 6390343593, "moments": "with-params",
+                "source_md5": "3e6a0fb74f28ce890dbede84cb62640c"}
 
 # Catch-up of the deferred Adam (one launch per step), algorithmic bytes: the claim flags of
 # the whole range are read (1 B per segment of 16 floats); every flagged segment reads and
@@ -69,7 +69,7 @@ LAZY_ENTRY_BYTES, LAZY_LOADED_BYTES, LAZY_PENDING_BYTES, LAZY_SHADOW_BYTES = 16,
 # taken on.
 CATCHUP_TRAFFIC = {"bytes": 9.084e9, "raw_bytes": 6.464e9, "params": 6390343593,
                    "batch": 1 << 18, "steps": 200, "moments": "with-params",
-                   "source_md5": "15eec88035e7f0c606f4974f8402c0d0"}
+                   "source_md5": "0776faf7250b6a6f6652e6775120f0c0"}
 
 # HBM bytes of one feature-extraction launch on the 480x720x120x100 volume from the two
 # counter passes (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000, the copy-calibrated factors);
@@ -870,9 +870,9 @@ ATOMIC_CEILING_GPS = 16.8
 # plain streaming copy of known size; valid only while the kernel sources
 # hashed in _fused_src_md5(), the optimiser state layout, the batch order, the
 # table reads and the decoder type are those the counters were taken with.
-FUSED_TRAFFIC = {"bytes": 20075089224, "raw_bytes": 11912743544, "moments": "with-params",
+FUSED_TRAFFIC = {"bytes": 19956565601, "raw_bytes": 11726266307, "moments": "with-params",
                  "sorted": True, "table_reads": "f32", "decoder": "f16", "coarse_lds": True,
-                 "source_md5": "14b8d4d63f82b0e95aecefef307e9e53"}
+                 "source_md5": "82e373832ab0f68f63aefe6efc3938b5"}
 
 
 def _fused_src_md5():
