@@ -51,39 +51,48 @@ struct Walk {
 };
 
 // Forward; row_bytes: of a table row.  us of a thread per sample / levels fastest /
-// level by level, 16 levels, F = 2, draw order:
-//                              100,003           262,144          1,048,576
-//   active, 240x360x60x50      309   300   259   821   780   621   3,395  3,076  2,356
-//   active, 121x90x61x20       195   238   167   535   610   383   2,337  2,409  1,451
-//   dense, 240x360x60x50       233   219   211   534   546   504   2,118  2,136  1,927
-//   hashed, 2^19 rows a level  147   200   117   282   504   238   1,082  1,975    849
-//   bricks, 240x360x60x50      314   380   350   826   961   781   3,637  3,653  2,798
-//   dense, fold 2, 8 levels     44    32    41    88    65    83     313    224    293
-// The table reads want level by level; the writes of enc, F floats of a line at a
-// time, want levels fastest, which wins where a batch is a few workgroups, from F = 4
-// on (8 levels, F = 8, 262,144 sorted samples 408 / 323 / 344; but of F = 4 a batch
-// of about one workgroup per CU on the smaller volume 113 / 121 / 104), on a dense
-// index of two features in cell order (359 / 311 / 347), and where the levels but the
-// largest fit the L2 of an XCD together (the last row).  A sample's lookups on bricks
-// are its longest part: a thread per sample from where every CU has one workgroup of
-// them (in cell order 100, 204 and 507 us there at F = 1, level by level 126, 220 and
-// 558).  On a dense or hashed index that holds only while no CU has a second one
-// (60,000 samples, hashed: 74.5 / 124 / 85).
+// level by level / in groups of 256 workgroups, 16 levels, FP32, F = 2:
+//                                             65,537 samples      262,144
+//   active, 240x360x60x50, draw order         147 183 160 152     596 717 548 594
+//   dense, 121x90x61x20, draw order            85 118  94  91     369 451 317 342
+//   hashed, 2^19 rows a level, draw order      73 136  80  79     308 530 238 308
+//   hashed, 2^14 rows a level, draw order      34  38  39  35     135 143 127 128
+//   hashed, 2^14 rows a level, sorted          27  25  23  20      64  91  63  53
+// Up to 40,960 samples the launch is a few hundred workgroups, and a sample's levels
+// side by side shorten its wait: levels fastest where the levels but the largest fit
+// the L2 of an XCD together, from F = 4 on, and on a dense index of two features; level
+// by level elsewhere.  Larger batches go in groups, whose part of a level's table and
+// of enc stays in the caches (active, 121x90x61x20, F = 1, 2^20 sorted samples 282 405
+// 282 216; dense, 60x45x30x10, F = 8, 8 levels, 2^18 sorted samples 63 93 66 66), but
+// for four levels or fewer over a table past the L2s, of which only the largest misses
+// them and the cheap ones hide behind it (active, 240x360x60x50, 150,000 samples 89 82
+// 82 85), and for a hashed table past them, whose reads are spread over a whole level,
+// so that the waves in flight share one as long as they can (the third row; 2^20
+// samples 1,437 2,097 874 1,192).  On bricks a sample's lookups are its longest part,
+// and where they miss the caches too, a thread per sample is ahead in draw order from
+// where every CU has one workgroup of them (F = 1, 65,537 and 100,003 samples, a thread
+// per sample and level by level: 240x360x60x50, 784 MiB of table, 160 and 192, 239 and
+// 274; 121x90x61x20, 65 MiB, 132 and 131, 182 and 178, sorted 120 and 65, 140 and 87);
+// past 2^19 samples groups are (the first volume, 2^20 samples 2,879 and 2,577, sorted
+// 969 and 850).
 inline Walk fwd_walk(const GridDev& g, int64_t n, int64_t row_bytes) {
-  const int by_level = (int)((n + 255) / 256);
+  const int by_level = (int)((n + 255) / 256), groups = by_level < 256 ? by_level : 256;
   if (n <= 4096) return {0};
-  if (g.lv[0].brick) return {n > 40960 ? -1 : by_level};
-  if (g.active)
-    return {g.F <= 2 || (g.F == 4 && n > 40960 && n <= 131072) ? by_level : 0};
+  const int64_t rows = g.last_pair + 2, bytes = rows * row_bytes;
+  if (g.lv[0].brick)
+    return {n > 524288 ? groups : n > 40960 && bytes > 80 << 20 ? -1 : by_level};
+  if (n > 40960) {
+    if (g.next_row) return {g.L <= 4 && bytes > 16 << 20 ? 0 : groups};
+    return {bytes > 10 << 20 && n > 81920 ? by_level : groups};
+  }
+  if (g.active) return {g.F <= 2 ? by_level : 0};
   if (g.next_row && g.F >= 2) return {0};
-  const int64_t rows = g.last_pair + 2;
   int64_t most = rows - g.lv[g.L - 1].slot_off;
   for (int l = 0; l + 1 < g.L; ++l) {
     const int64_t r = g.lv[l + 1].slot_off - g.lv[l].slot_off;
     if (r > most) most = r;
   }
-  if ((rows - most) * row_bytes <= 4 << 20) return {0};
-  return {n > 40960 && n <= 65536 ? -1 : by_level};
+  return {(rows - most) * row_bytes <= 4 << 20 ? 0 : by_level};
 }
 
 // Backward.  A batch in cell order wants the waves in flight on one level: lanes of

@@ -1,7 +1,7 @@
 """The separate encoding at the batch sizes where its launch walks samples and levels
-another way (4,096, 40,960, 65,536 and 131,072 samples; groups of 65,536, and of
-32,768 above 524,288): forward bit for bit, and backward with positive terms only, against the same
-batch in calls of 999 samples."""
+another way (4,096, 40,960, 81,920 and 524,288 samples; groups of 65,536, in the
+backward of 32,768 too): forward bit for bit, and backward with positive terms only,
+against the same batch in calls of 999 samples."""
 import numpy as np
 import pytest
 import torch
@@ -28,6 +28,8 @@ def _index(fl, kind, F):
         return fl.fhash_hash_index(fl.grid_desc(RES, F), 12)[0], None
     if kind == "large hash":  # its levels do not fit one L2 together
         return fl.fhash_hash_index(fl.grid_desc([[40, 40, 40, 40]] * 4, F), 20)[0], None
+    if kind == "large dense":  # past the L2s, in four levels
+        return fl.fhash_dense_index(fl.grid_desc([[60, 50, 40, 10]] * 4, F))[0], None
     m = (np.random.default_rng(2).random(DIMS[::-1]) < 0.002).astype(np.uint8)
     bits = torch.from_numpy(synth.pack_mask_rows(m).view(np.int64)).cuda()
     lay = fl.LAYOUT_BRICKS if kind == "bricks" else fl.LAYOUT_ROWS
@@ -35,9 +37,10 @@ def _index(fl, kind, F):
     return idx, dirs
 
 
-@pytest.mark.parametrize("n", [1, 257, 4096, 4097, 32769, 40960, 40961, 65537, 131073, 524289])
+@pytest.mark.parametrize("n", [1, 257, 4096, 4097, 32769, 40960, 40961, 65537, 81921, 131073,
+                               524289])
 @pytest.mark.parametrize("F", [1, 2, 4, 8])
-@pytest.mark.parametrize("kind", ["active", "hash", "large hash", "bricks"])
+@pytest.mark.parametrize("kind", ["active", "large dense", "hash", "large hash", "bricks"])
 def test_every_walk_gives_the_same(fl, kind, F, n):
     idx, _keep = _index(fl, kind, F)
     L = len(RES)
