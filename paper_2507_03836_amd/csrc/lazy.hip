@@ -225,10 +225,8 @@ __device__ __forceinline__ void claim_pair(int64_t s0, int64_t s1, bool v0, bool
 // level per row of the grid: its constants are wave-uniform, a wave's flag stores fall
 // into one level (neighbouring samples of a sorted batch often into the same lines),
 // and a sample's levels wait for their directory entries side by side instead of one
-// after another.  On bricks, a large batch has the waves for that wait, and one row of
-// the grid with a loop over the levels is ahead in cell order (262,144 samples, 16
-// levels: 226 us, a row per level 250; in draw order 508 and 492; 30,000 sorted 151
-// and 56).
+// after another.  On bricks a level's lookups are many, and a grid row for each of
+// them does not suit every batch (mark_rows).
 template <bool BRICK>
 __global__ void __launch_bounds__(256)
     lazy_mark_kernel(GridDev g, int l0, int l1, const float4* __restrict__ pos, int64_t n,
@@ -587,6 +585,25 @@ hipError_t launch_lazy_init(const fhash_lazy* lz, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Grid rows of the mark on bricks.  Up to 57,344 samples a row per level shortens the
+// wait; larger batches have the waves for it, and fewer levels at a time leave more of
+// their directory and flags in the caches.  us with 1 / 2 / 4 / 8 rows and a row per
+// level, 16 levels, 240x360x60x50 (26 MB of flags, draw order and sorted): 50,000
+// samples 89 64 73 74 74 and 85 54 46 46 48; 90,000 110 103 119 119 119 and 94 68 71 72
+// 73; 131,072 131 155 169 166 168 and 97 89 95 89 95; 200,000 245 262 237 228 238 and 127
+// 129 111 111 128; 262,144 294 322 288 286 301 and 135 141 125 130 150; 524,288 695 633
+// 510 525 554 and 189 174 169 197 227.  With 2 MB of flags (121x90x61x20) eight rows are
+// ahead at every size: 131,072 92 82 84 77 85 and 72 48 42 39 39, 262,144 155 161 145 144
+// 149 and 96 77 70 68 68.
+static int mark_rows(int64_t n, int levels, int64_t flags) {
+  const int most = n <= 57344 ? levels
+                   : flags <= 8 << 20 ? 8
+                   : n <= 98304 ? 2
+                   : n <= 163840 ? 1
+                                 : 4;
+  return most < levels ? most : levels;
+}
+
 hipError_t launch_lazy_prepare(const GridDev& g, int l0, int l1, const float* pos, int64_t n,
                                const fhash_lazy* lz, float* p, float* gr, float* m, float* v,
                                void* shadow, fhash_dtype sdt, uint32_t phases, hipStream_t st) {
@@ -597,8 +614,8 @@ hipError_t launch_lazy_prepare(const GridDev& g, int l0, int l1, const float* po
     if (b > 4096) b = 4096;
     const bool brick = g.lv[0].brick;
     auto kern = brick ? lazy_mark_kernel<true> : lazy_mark_kernel<false>;
-    const unsigned rows = brick && n > 131072 ? 1 : (unsigned)(l1 - l0);
-    hipLaunchKernelGGL(kern, dim3((unsigned)b, rows), dim3(256), 0, st, g, l0, l1,
+    const int rows = brick ? mark_rows(n, l1 - l0, (lz->end - lz->begin) / kSeg) : l1 - l0;
+    hipLaunchKernelGGL(kern, dim3((unsigned)b, (unsigned)rows), dim3(256), 0, st, g, l0, l1,
                        reinterpret_cast<const float4*>(pos), n, w.flags, lz->begin, lz->end);
   }
   // at most 9 segments per sample and level (8 row pairs, one may straddle)
