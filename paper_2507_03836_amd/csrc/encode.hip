@@ -19,7 +19,7 @@ namespace {
 //  > 0: one thread per sample and level, that many workgroups of 256 samples
 //     through one level after another, then the next as many: the waves in flight
 //     share a level and its part of the table stays in the caches.
-//  < 0: one thread per sample with a loop over its levels.
+//  < 0: one thread per sample with a loop over its levels (bricks).
 struct Walk {
   int chunk;
   // workgroups for n samples of L levels
@@ -241,11 +241,9 @@ void launch_fwd_tt(const GridDev& g, const float* pos, int64_t n, const T* table
   const Walk walk = fwd_walk(g, n, F * sizeof(T));
   const dim3 grid(walk.blocks(n, g.L));
   const float4* p = reinterpret_cast<const float4*>(pos);
-  const bool brick = g.lv[0].brick;
-  auto kern = walk.chunk < 0 ? (brick ? encode_fwd_kernel<F, T, true, true>
-                                      : encode_fwd_kernel<F, T, false, true>)
-                             : (brick ? encode_fwd_kernel<F, T, true, false>
-                                      : encode_fwd_kernel<F, T, false, false>);
+  auto kern = !g.lv[0].brick  ? encode_fwd_kernel<F, T, false, false>
+              : walk.chunk < 0 ? encode_fwd_kernel<F, T, true, true>
+                               : encode_fwd_kernel<F, T, true, false>;
   hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, g, walk, p, n, table, enc);
 }
 
